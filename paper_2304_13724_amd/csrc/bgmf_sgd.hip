@@ -790,6 +790,10 @@ __global__ void __launch_bounds__(256) k_sgd_lds(SgdParams P) {
 // persistent schedule, where a column-block moves between waves (and XCDs)
 // inside one launch; a launch of one stratum touches every column from one
 // wave only and uses plain cached accesses.
+//
+// Long runs of one row or one column (heavy users and items, which hold the
+// longest blocks of a stratum) take a shorter step of their own; it needs
+// plain accesses to both matrices, so only the launch-per-stratum form has it.
 template <int KP, bool MASK, bool COH>
 __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
   using L = Lanes<KP, MASK>;
@@ -799,6 +803,14 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
   constexpr int CH = D;
   static_assert(D == 16, "the window holds the previous chunk, the current one and the next two");
   constexpr int VPOL = COH ? kCoherent : 0;
+  // Shortest run swept as one, and shortest block in which runs are looked
+  // for.  Entering and leaving a run each wait for its first rows (about
+  // 1 us together, what 32 ratings gain): runs from 16 up take 111.8 ms per
+  // epoch of 100M ratings at k = 128, p = 2048, from 24 up 110.3 ms, from 32
+  // up 109.0 ms (and 116.8, 117.1, 117.1 ms at 20M ratings, k = 64, p = 4096).
+  constexpr int kRunMin = 32;
+  constexpr int kRunBlock = 48;
+  constexpr int kRunRow = 1, kRunCol = 2;
   constexpr uint32_t kNoCol = 0xFFFFFFFFu;  // column of ratings before the block: matches none
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int b = row_block_of_wave(P, wave);
@@ -841,29 +853,40 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
     //   wcol = byte offset of the column in the slice of V (0 past the end,
     //          kNoCol before the start)
     //   wx   = x / KPL
+    // The block is swept in segments (see below); t0 is the current one's
+    // first rating, and ratings before it match no column.
+    int32_t t0 = 0;
     uint32_t wrow = 0u, wcol = 0u;
     float wx = 0.0f;
     auto decode = [&](uint2 w, int32_t c) {
       const int32_t t = c - CH + lane;
-      const bool ok = t >= 0 && t < len;
+      const bool ok = t >= t0 && t < len;
       wrow = ok ? (w.x & kRowMask) * rowbytes : 0u;
-      wcol = ok ? ((w.x >> kColShift) & kColMask) * rowbytes : (t < 0 ? kNoCol : 0u);
+      wcol = ok ? ((w.x >> kColShift) & kColMask) * rowbytes : (t < t0 ? kNoCol : 0u);
       wx = __uint_as_float(w.y) * xscale;
     };
 
     float ring[D][NV], vring[D][NV];
     uint32_t ringrow[D];
     uint2 Wn1 = make_uint2(0u, 0u);
+    auto open = [&](int32_t t) {
+      t0 = t;
+      decode(rp[t + (lane >= CH ? lane - CH : 0)], t);
+      Wn1 = rp[t + lane];  // window of chunk t + CH
+    };
     auto prime = [&]() {
-      decode(rp[lane >= CH ? lane - CH : 0], 0);
-      Wn1 = rp[lane];  // window of chunk CH
 #pragma unroll
       for (int j = 0; j < D; ++j) {
         ringrow[j] = rl(wrow, CH + j);
         ld_row<NV, 0>(ring[j], Ures, doff, ringrow[j]);
       }
     };
-    if (len > 0) prime();
+    // blocks in which runs are looked for (see below)
+    const bool runs = !COH && len >= kRunBlock;
+    if (len > 0) {
+      open(0);
+      if (!runs) prime();
+    }
     if (s > P.s_begin) {
       const int nb = (b + 1 == P.p) ? 0 : b + 1;
       if (!wait_progress(P.flags + (int64_t)nb * kFlagStride, g, P.wait_ticks)) {
@@ -875,11 +898,171 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
     if (len > 0) {
       const __amdgpu_buffer_rsrc_t Vres = __builtin_amdgcn_make_buffer_rsrc(
           P.V + c0 * k, (short)0, (int)((uint32_t)ncols * rowbytes), kBufWord3);
+      // Runs: kRunMin or more consecutive ratings of one row (a heavy user
+      // in the block) or of one column (a heavy item).  The run's own row of
+      // U or V (w) stays in registers from its first rating to its last; the
+      // partner rows of the other matrix (z), all different, come through
+      // the ring.  The step needs no lookup of recent results, one load, one
+      // store and three lane reads instead of six, and no choice between
+      // operands, so it runs at the pace of its dependency chain (66 ns per
+      // rating at k = 64 and 80 ns at k = 128, against 106 and 120 ns of the
+      // general step, which is bound by its issue slots); the arithmetic is
+      // the general step's, so the results are the same bits.
+      // A partner that repeats within the prefetch distance (a duplicate
+      // rating) ends the run before the chunk in which it would be stale.
+      //
+      // run_at: does a run start at rating c (the window's lane CH)?
+      auto run_at = [&](int32_t c) -> int {
+        if (len - c < kRunMin) return 0;
+        constexpr uint64_t kAll = ((1ull << kRunMin) - 1ull) << CH;
+        static_assert(kRunMin >= CH && CH + kRunMin <= 64, "the window shows a run's first ratings");
+        const uint64_t rows = __builtin_amdgcn_ballot_w64(wrow == rl(wrow, CH));
+        if ((rows & kAll) == kAll) return kRunRow;
+        const uint64_t cols = __builtin_amdgcn_ballot_w64(wcol == rl(wcol, CH));
+        return (cols & kAll) == kAll ? kRunCol : 0;
+      };
+      // Sweeps the run that starts at t (whose window is decoded); returns
+      // the first rating after it, or t if its first chunk has a duplicate.
+      auto run = [&](int32_t t, bool by_row) -> int32_t {
+        const auto rows_of = [&](bool of_v) {  // the block's rows of V or U
+          const int64_t base = reinterpret_cast<int64_t>(of_v ? P.V + c0 * k : P.U + r0 * k);
+          const uint32_t bytes = (of_v ? (uint32_t)ncols : rows_b) * rowbytes;
+          return __builtin_amdgcn_make_buffer_rsrc(
+              reinterpret_cast<float *>(uniform64(base)), (short)0,
+              __builtin_amdgcn_readfirstlane((int)bytes), kBufWord3);
+        };
+        const __amdgpu_buffer_rsrc_t Zres = rows_of(by_row), Wres = rows_of(!by_row);
+        const uint32_t own = rl(by_row ? wrow : wcol, CH);
+        uint32_t wz = by_row ? wcol : wrow;  // partner offsets of the window
+        uint32_t dup = 0;
+        float w[NV], z[NV], pnz[NV];
+        ld_row<NV, 0>(w, Wres, doff, own);
+#pragma unroll
+        for (int j = 0; j < D; ++j) {
+          ringrow[j] = rl(wz, CH + j);
+          ld_row<NV, 0>(ring[j], Zres, doff, ringrow[j]);
+          dup |= (uint32_t)(__builtin_amdgcn_ballot_w64(wz == ringrow[j]) >> CH) & ((1u << j) - 1u);
+        }
+        if (dup) return t;
+        float x64 = __uint_as_float(rl(__float_as_uint(wx), CH));
+        uint32_t poff = ringrow[0];
+        __builtin_amdgcn_s_waitcnt(0x0F70);
+#pragma unroll
+        for (int v = 0; v < NV; ++v) {
+          z[v] = ring[0][v];
+          pnz[v] = z[v];  // the first pending store writes rating t's row back unchanged
+        }
+        auto step_chunk = [&](auto tail_tag, int32_t c, int32_t count) {
+          constexpr bool TAIL = decltype(tail_tag)::value;
+          const int32_t left = TAIL ? tail_left(count, 0) : CH;
+          const uint2 Wn2 = rp[c + CH + lane];
+#pragma unroll
+          for (int j = 0; j < CH; ++j) {
+            const int slot = (j == 0) ? CH - 1 : j - 1;  // ring slot of the previous rating
+            const int next = (j + 1) % CH;
+            float tt = fmaf(-w[0], z[0], x64);
+#pragma unroll
+            for (int v = 1; v < NV; ++v) tt = fmaf(-w[v], z[v], tt);
+            pin();
+            st_row<NV, 0>(pnz, Zres, doff, poff);
+            pin();
+            tt = tt + dpp_mov<0xB1>(tt);  // quad_perm [1,0,3,2]
+            pin();
+            // the partner of the rating D after the previous one
+            ringrow[slot] = rl(wz, 2 * CH + j - 1);
+            pin();
+            tt = tt + dpp_mov<0x4E>(tt);  // quad_perm [2,3,0,1]
+            pin();
+            float dw[NV], dz[NV];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) dw[v] = nab * w[v];
+            const uint64_t hit = __builtin_amdgcn_ballot_w64(wz == ringrow[slot]);
+            pin();
+            tt = tt + dpp_mov<0x141>(tt);  // row_half_mirror
+            pin();
+#pragma unroll
+            for (int v = 0; v < NV; ++v) dz[v] = nab * z[v];
+            const float x64n = __uint_as_float(rl(__float_as_uint(wx), CH + j + 1));
+            pin();
+            tt = tt + dpp_mov<0x140>(tt);  // row_mirror
+            pin();
+            ld_row<NV, 0>(ring[slot], Zres, doff, ringrow[slot]);
+            pin();
+            if constexpr (KPL >= 32) tt = tt + dpp_mov<0x142>(tt);  // row_bcast:15
+            pin();
+            // the row loaded above is stale if one of the 15 ratings before
+            // it has the same partner (their stores come later); the empty
+            // asm keeps the test in this step's gaps.  (The load of step 0
+            // is for this chunk's last rating, tested before the chunk.)
+            if (j > 0) {
+              dup |= (uint32_t)(hit >> (CH + j)) & ((1u << (D - 1)) - 1u);
+              asm volatile("" : "+s"(dup));
+            }
+            pin();
+            if constexpr (KPL >= 64) tt = tt + dpp_mov<0x143>(tt);  // row_bcast:31
+            pin();
+            const float e = __uint_as_float(rl(__float_as_uint(tt), 63));
+            pin();
+            const float ae = alpha * e;
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+              pnz[v] = z[v] + fmaf(ae, w[v], dz[v]);
+              w[v] = w[v] + fmaf(ae, z[v], dw[v]);
+              z[v] = ring[next][v];
+            }
+            poff = ringrow[j];
+            x64 = x64n;
+            pin();
+            if constexpr (TAIL) {
+              if (j + 1 >= left) break;
+            }
+          }
+          decode(Wn1, c + CH);
+          Wn1 = Wn2;
+          wz = by_row ? wcol : wrow;
+          // the load of the next chunk's step 0
+          const uint64_t hit =
+              __builtin_amdgcn_ballot_w64(wz == rl(wz, 2 * CH - 1));
+          dup |= (uint32_t)(hit >> CH) & ((1u << (D - 1)) - 1u);
+        };
+        // ratings of the run from c on, as far as the window shows
+        auto lead = [&](int32_t c) -> int32_t {
+          const uint64_t same =
+              __builtin_amdgcn_ballot_w64((by_row ? wrow : wcol) == own) >> CH;
+          return __builtin_amdgcn_readfirstlane(min((int32_t)__builtin_ctzll(~same), len - c));
+        };
+        int32_t c = t, left = lead(t);
+        while (left >= CH) {
+          step_chunk(std::false_type{}, c, CH);
+          c += CH;
+          left = dup ? 0 : lead(c);
+        }
+        if (left > 0) {
+          step_chunk(std::true_type{}, c, left);
+          c += left;
+        }
+        st_row<NV, 0>(pnz, Zres, doff, poff);
+        st_row<NV, 0>(w, Wres, doff, own);
+        return c;
+      };
       // GPU_STEPS passes over the block (Section 1.3); each pass re-reads the
       // U and V rows this wave stored in the previous one (the hardware keeps
       // a wave's accesses to one address in order)
       for (int pass = 0; pass < P.passes; ++pass) {
-      if (pass > 0) prime();
+      int32_t seg = 0;
+      while (seg < len) {
+      if (pass > 0 || seg > 0) open(seg);
+      if constexpr (!COH) {
+        if (runs) {
+          const int kind = run_at(seg);
+          const int32_t next = kind ? run(seg, __builtin_amdgcn_readfirstlane(kind) == kRunRow) : seg;
+          if (next > seg) {
+            seg = next;
+            continue;
+          }
+        }
+      }
+      if (runs || pass > 0) prime();
 #pragma unroll
       for (int j = 0; j < D; ++j) ld_row<NV, VPOL>(vring[j], Vres, doff, rl(wcol, CH + j));
       uint32_t prev_row = 0xFFFFFFFFu;
@@ -1062,16 +1245,32 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
         decode(Wn1, c + CH);
         Wn1 = Wn2;
       };
-      const int32_t full = len & ~(CH - 1);
+      // full chunks up to the block's end or the start of a run, then the
+      // last, partial chunk
+      int32_t c = seg;
+      bool stop = false;
+      while (c + CH <= len) {
+        if constexpr (NV == 1) chunk_pinned(std::false_type{}, c);
+        else chunk(std::false_type{}, c);
+        c += CH;
+        if constexpr (!COH) {
+          if (runs && run_at(c)) {
+            stop = true;
+            break;
+          }
+        }
+      }
+      if (!stop && c < len) {
+        if constexpr (NV == 1) chunk_pinned(std::true_type{}, c);
+        else chunk(std::true_type{}, c);
+        c = len;
+      }
       if constexpr (NV == 1) {
-        for (int32_t c = 0; c < full; c += CH) chunk_pinned(std::false_type{}, c);
-        if (full < len) chunk_pinned(std::true_type{}, full);
         // the last rating's results
         st_row<NV, 0>(pnu, Ures, doff, prow);
         st_row<NV, VPOL>(pnv, Vres, doff, pcol);
-      } else {
-        for (int32_t c = 0; c < full; c += CH) chunk(std::false_type{}, c);
-        if (full < len) chunk(std::true_type{}, full);
+      }
+      seg = c;
       }
       }
     }
