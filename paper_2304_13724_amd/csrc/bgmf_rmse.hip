@@ -8,6 +8,7 @@
 // are combined in a fixed order by a second kernel, so the result does not
 // depend on scheduling.
 #include <algorithm>
+#include <type_traits>
 
 #include "bgmf_internal.h"
 
@@ -28,102 +29,143 @@ __device__ __forceinline__ float dpp_mov(float x) {
 // Lanes per rating: from k = 32 up, each lane holds four float4 slices of
 // u_i and of v_j (KP/16 lanes per rating), which keeps the cross-lane levels
 // and the per-rating index work per wave step low; at k = 16 four lanes
-// hold one slice each.  Wave steps whose loads are in flight together: two
-// at four slices per lane, eight at one.
+// hold one slice each.  Twice or half as many lanes are slower (100M ratings,
+// k = 64: 1.58 and 1.56 ms against 1.34).
 template <int KP>
 constexpr int rmse_lanes() { return KP >= 32 ? KP / 16 : KP / 4; }
+// Wave steps whose loads are in flight together.  With U in LDS one
+// workgroup fills a CU, and three steps beat two and one (1.30, 1.34, 1.31
+// ms); without, more waves per CU beat more steps per wave (one step against
+// two: 6.6 against 7.3 ms at 100M ratings, k = 128, p = 2048).
 template <int KP>
-constexpr int rmse_unroll() { return KP >= 32 ? 2 : 8; }
+constexpr int rmse_unroll() { return KP >= 64 ? 1 : KP >= 32 ? 2 : 8; }
+template <int KP>
+constexpr int rmse_unroll_lds() { return KP >= 32 ? 3 : 8; }
 
-// KP: padded k; L lanes per rating; each lane covers the float4 slices
-// q = g, g + L, ... of the row.
-template <int KP>
+// Factor rows are addressed in bytes: a 64-bit base plus row * rowbytes is
+// one multiply-add.
+__device__ __forceinline__ const char *row_ptr(const float *base, uint32_t row, uint32_t rowbytes) {
+  return reinterpret_cast<const char *>(base) + (uint64_t)row * rowbytes;
+}
+
+// The lane's share of the dot product of u_i and v_j: its float4 slices
+// q = gl, gl + L, ... of both rows.  FULL: k = KP.  Otherwise a slice past k
+// reads slice 0 (so no load needs a branch) and counts as zero.
+template <int KP, bool FULL>
+struct Dot {
+  static constexpr int L = rmse_lanes<KP>();  // lanes per rating
+  static constexpr int QL = KP / 4 / L;       // slices per lane
+  uint32_t off[FULL ? 1 : QL];                // byte offset of each slice in a row
+  bool in[FULL ? 1 : QL];
+  __device__ __forceinline__ Dot(int gl, int32_t k) {
+    if constexpr (FULL) {
+      off[0] = (uint32_t)gl * 16u;
+    } else {
+#pragma unroll
+      for (int i = 0; i < QL; ++i) {
+        in[i] = 4 * (gl + i * L) < k;
+        off[i] = in[i] ? (uint32_t)(gl + i * L) * 16u : 0u;
+      }
+    }
+  }
+  __device__ __forceinline__ uint32_t at(int i) const {
+    if constexpr (FULL) return off[0] + (uint32_t)(i * L) * 16u;
+    else return off[i];
+  }
+  __device__ __forceinline__ void load(float4 (&x)[QL], const char *row) const {
+#pragma unroll
+    for (int i = 0; i < QL; ++i) x[i] = *reinterpret_cast<const float4 *>(row + at(i));
+  }
+  // x - u.v, in every lane of the rating's group
+  __device__ __forceinline__ float error(float x, const float4 (&a)[QL], const float4 (&c)[QL]) const {
+    float part = 0.0f;
+#pragma unroll
+    for (int i = 0; i < QL; ++i) {
+      float t = part;
+      t = fmaf(a[i].x, c[i].x, t);
+      t = fmaf(a[i].y, c[i].y, t);
+      t = fmaf(a[i].z, c[i].z, t);
+      t = fmaf(a[i].w, c[i].w, t);
+      if constexpr (FULL) part = t;
+      else part = in[i] ? t : part;
+    }
+    part += dpp_mov<0xB1>(part);
+    if constexpr (L > 2) part += dpp_mov<0x4E>(part);
+    if constexpr (L > 4) part += dpp_mov<0x141>(part);
+    if constexpr (L > 8) part += dpp_mov<0x140>(part);
+    return x - part;
+  }
+};
+
+// Every lane of a group adds the group's squares, so the wave's total is L
+// times the sum (an exact scaling).
+template <int L>
+__device__ __forceinline__ double wave_sum(double acc) {
+  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+  return acc * (1.0 / L);
+}
+
+// KP: k rounded up to a power of two.
+template <int KP, bool FULL>
 __global__ void __launch_bounds__(256)
 k_rmse_partial(const uint2 *__restrict__ rec, const int64_t *__restrict__ wblock_ptr,
                const float *__restrict__ U, const float *__restrict__ V, Grid G, int32_t k,
                double *__restrict__ partials) {
-  const int32_t p = G.p;
-  constexpr int L = rmse_lanes<KP>();  // lanes per rating
-  constexpr int RPS = 64 / L;                // ratings per wave step
-  constexpr int Q = KP / 4;                  // float4 slices per padded row
-  constexpr int QL = (Q + L - 1) / L;        // slices per lane
+  using Dt = Dot<KP, FULL>;
+  constexpr int L = Dt::L, QL = Dt::QL;
+  constexpr int RPS = 64 / L;             // ratings per wave step
   constexpr int UNR = rmse_unroll<KP>();  // wave steps whose loads are in flight together
+  const int32_t p = G.p;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int gl = lane % L, grp = lane / L;
+  const int grp = lane / L;
+  const Dt dot(lane % L, k);
+  const uint32_t rowbytes = (uint32_t)k * 4u;
   const int b = blockIdx.x % p;    // row-block
   const int cg = blockIdx.x / p;   // group of column-blocks
   const int c_end = min(p, (cg + 1) * kRmseColGroup);
   const float *Ub = U + G.row_start(b) * k;
   const uint32_t rmax = (uint32_t)(G.row_start(b + 1) - G.row_start(b)) - 1u;
-  const int kq = k / 4;
   double acc = 0.0;
   for (int c = cg * kRmseColGroup + wave; c < c_end; c += kWavesPerGroup) {
     const int s = (c - b + p) % p;  // block (b, c) is in stratum s
     const int64_t beg = wblock_ptr[(int64_t)b * p + s];
     const int64_t end = wblock_ptr[(int64_t)b * p + s + 1];
     if (beg == end) continue;
-    const int C = (b + s) % p;
-    const float *Vb = V + G.col_start(C) * k;
-    const uint32_t cmax = (uint32_t)(G.col_start(C + 1) - G.col_start(C)) - 1u;
+    const float *Vb = V + G.col_start(c) * k;
+    const uint32_t cmax = (uint32_t)(G.col_start(c + 1) - G.col_start(c)) - 1u;
+    const int32_t len = (int32_t)(end - beg);
+    const uint2 *rb = rec + beg;
     // records of the next iteration are loaded one iteration ahead, so the
     // factor-row loads never wait for a record load
     uint2 rn[UNR];
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
-      const int64_t t = beg + u * RPS + grp;
-      rn[u] = rec[t < end ? t : beg];
+      const int32_t t = u * RPS + grp;
+      rn[u] = rb[t < len ? t : 0];
     }
-    for (int64_t t0 = beg; t0 < end; t0 += RPS * UNR) {
-      float4 a[UNR][QL], c[UNR][QL];
+    for (int32_t t0 = 0; t0 < len; t0 += RPS * UNR) {
+      float4 ua[UNR][QL], va[UNR][QL];
       float x[UNR];
-      bool ok[UNR];
-      uint2 r[UNR];
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
-        r[u] = rn[u];
-        const int64_t t = t0 + RPS * UNR + u * RPS + grp;
-        rn[u] = rec[t < end ? t : beg];
+        x[u] = __uint_as_float(rn[u].y);
+        dot.load(ua[u], row_ptr(Ub, min(rn[u].x & kRowMask, rmax), rowbytes));
+        dot.load(va[u], row_ptr(Vb, min((rn[u].x >> kColShift) & kColMask, cmax), rowbytes));
       }
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
-        const int64_t t = t0 + u * RPS + grp;
-        ok[u] = t < end;
-        x[u] = __uint_as_float(r[u].y);
-        const uint32_t row = min(r[u].x & kRowMask, rmax);
-        const uint32_t col = min((r[u].x >> kColShift) & kColMask, cmax);
-        const float4 *up = reinterpret_cast<const float4 *>(Ub + (int64_t)row * k);
-        const float4 *vp = reinterpret_cast<const float4 *>(Vb + (int64_t)col * k);
-#pragma unroll
-        for (int i = 0; i < QL; ++i) {
-          // branch-free: slices past k read slice 0 and are zeroed after
-          const int q = gl + i * L;
-          const bool in = q < kq;
-          const int qc = in ? q : 0;
-          a[u][i] = up[qc];
-          c[u][i] = vp[qc];
-          if (!in) a[u][i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
+        const int32_t t = t0 + (UNR + u) * RPS + grp;
+        rn[u] = rb[t < len ? t : 0];
       }
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
-        float part = 0.0f;
-#pragma unroll
-        for (int i = 0; i < QL; ++i) {
-          part = fmaf(a[u][i].x, c[u][i].x, part);
-          part = fmaf(a[u][i].y, c[u][i].y, part);
-          part = fmaf(a[u][i].z, c[u][i].z, part);
-          part = fmaf(a[u][i].w, c[u][i].w, part);
-        }
-        part += dpp_mov<0xB1>(part);
-        if constexpr (L > 2) part += dpp_mov<0x4E>(part);
-        if constexpr (L > 4) part += dpp_mov<0x141>(part);
-        if constexpr (L > 8) part += dpp_mov<0x140>(part);
-        const float d = (ok[u] && gl == 0) ? x[u] - part : 0.0f;
+        float d = dot.error(x[u], ua[u], va[u]);
+        d = t0 + u * RPS + grp < len ? d : 0.0f;
         acc = fma((double)d, (double)d, acc);
       }
     }
   }
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+  acc = wave_sum<L>(acc);
   if (lane == 0) partials[(int64_t)blockIdx.x * kWavesPerGroup + wave] = acc;
 }
 
@@ -132,76 +174,53 @@ k_rmse_partial(const uint2 *__restrict__ rec, const int64_t *__restrict__ wblock
 // (b, s), s = s0 + y, s0 + y + gridDim.y, ..., to partials[y p + b] (each
 // partial is owned by one wave per launch, and launches are ordered on the
 // stream).
-template <int KP>
+template <int KP, bool FULL>
 __global__ void __launch_bounds__(256)
 k_rmse_stratum(const uint2 *__restrict__ rec, int64_t rec_origin,
                const int64_t *__restrict__ block_ptr, int32_t s0, int32_t s1,
                const float *__restrict__ U, const float *__restrict__ V, Grid G, int32_t k,
                double *__restrict__ partials) {
-  const int32_t p = G.p;
-  constexpr int L = rmse_lanes<KP>();
+  using Dt = Dot<KP, FULL>;
+  constexpr int L = Dt::L, QL = Dt::QL;
   constexpr int RPS = 64 / L;
-  constexpr int Q = KP / 4;
-  constexpr int QL = (Q + L - 1) / L;
   constexpr int UNR = rmse_unroll<KP>();
+  const int32_t p = G.p;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int gl = lane % L, grp = lane / L;
+  const int grp = lane / L;
+  const Dt dot(lane % L, k);
+  const uint32_t rowbytes = (uint32_t)k * 4u;
   const int b = blockIdx.x * kWavesPerGroup + wave;
   if (b >= p) return;
   const float *Ub = U + G.row_start(b) * k;
   const uint32_t rmax = (uint32_t)(G.row_start(b + 1) - G.row_start(b)) - 1u;
-  const int kq = k / 4;
   double acc = 0.0;
   for (int32_t s = s0 + (int32_t)blockIdx.y; s < s1; s += (int32_t)gridDim.y) {
-  const int64_t beg = block_ptr[(int64_t)s * p + b] - rec_origin;
-  const int64_t end = block_ptr[(int64_t)s * p + b + 1] - rec_origin;
-  const int C = (b + s) % p;
-  const float *Vb = V + G.col_start(C) * k;
-  const uint32_t cmax = (uint32_t)(G.col_start(C + 1) - G.col_start(C)) - 1u;
-  for (int64_t t0 = beg; t0 < end; t0 += RPS * UNR) {
-    float4 a[UNR][QL], c[UNR][QL];
-    float x[UNR];
-    bool ok[UNR];
+    const int64_t beg = block_ptr[(int64_t)s * p + b];
+    const int32_t len = (int32_t)(block_ptr[(int64_t)s * p + b + 1] - beg);
+    const uint2 *rb = rec + (beg - rec_origin);
+    const int C = (b + s) % p;
+    const float *Vb = V + G.col_start(C) * k;
+    const uint32_t cmax = (uint32_t)(G.col_start(C + 1) - G.col_start(C)) - 1u;
+    for (int32_t t0 = 0; t0 < len; t0 += RPS * UNR) {
+      float4 ua[UNR][QL], va[UNR][QL];
+      float x[UNR];
 #pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      const int64_t t = t0 + u * RPS + grp;
-      ok[u] = t < end;
-      const uint2 r = rec[ok[u] ? t : beg];
-      x[u] = __uint_as_float(r.y);
-      const uint32_t row = min(r.x & kRowMask, rmax);
-      const uint32_t col = min((r.x >> kColShift) & kColMask, cmax);
-      const float4 *up = reinterpret_cast<const float4 *>(Ub + (int64_t)row * k);
-      const float4 *vp = reinterpret_cast<const float4 *>(Vb + (int64_t)col * k);
+      for (int u = 0; u < UNR; ++u) {
+        const int32_t t = t0 + u * RPS + grp;
+        const uint2 r = rb[t < len ? t : 0];
+        x[u] = __uint_as_float(r.y);
+        dot.load(ua[u], row_ptr(Ub, min(r.x & kRowMask, rmax), rowbytes));
+        dot.load(va[u], row_ptr(Vb, min((r.x >> kColShift) & kColMask, cmax), rowbytes));
+      }
 #pragma unroll
-      for (int i = 0; i < QL; ++i) {
-        const int q = gl + i * L;
-        const bool in = q < kq;
-        const int qc = in ? q : 0;
-        a[u][i] = up[qc];
-        c[u][i] = vp[qc];
-        if (!in) a[u][i] = make_float4(0.f, 0.f, 0.f, 0.f);
+      for (int u = 0; u < UNR; ++u) {
+        float d = dot.error(x[u], ua[u], va[u]);
+        d = t0 + u * RPS + grp < len ? d : 0.0f;
+        acc = fma((double)d, (double)d, acc);
       }
     }
-#pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      float part = 0.0f;
-#pragma unroll
-      for (int i = 0; i < QL; ++i) {
-        part = fmaf(a[u][i].x, c[u][i].x, part);
-        part = fmaf(a[u][i].y, c[u][i].y, part);
-        part = fmaf(a[u][i].z, c[u][i].z, part);
-        part = fmaf(a[u][i].w, c[u][i].w, part);
-      }
-      part += dpp_mov<0xB1>(part);
-      if constexpr (L > 2) part += dpp_mov<0x4E>(part);
-      if constexpr (L > 4) part += dpp_mov<0x141>(part);
-      if constexpr (L > 8) part += dpp_mov<0x140>(part);
-      const float d = (ok[u] && gl == 0) ? x[u] - part : 0.0f;
-      acc = fma((double)d, (double)d, acc);
-    }
   }
-  }
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+  acc = wave_sum<L>(acc);
   if (lane == 0) partials[(int64_t)blockIdx.y * p + b] += acc;
 }
 
@@ -211,54 +230,70 @@ k_rmse_stratum(const uint2 *__restrict__ rec, int64_t rec_origin,
 // row or column lies outside the matrix, or whose value is not finite, adds
 // nothing and sets a bit of *bad (1: index, 2: value); its factor rows are
 // not read.
+//
+// The rows of U and V are random reads, so the kernel is bound by how many
+// of them are in flight: a wave has the rows of kCooUnroll steps outstanding
+// and reads the indices of the steps after them meanwhile (10M ratings,
+// k = 64: 474 us with one step and its indices in turn, 449 with indices
+// ahead, 430 with two steps).
 template <int KP>
+constexpr int kCooUnroll = KP >= 32 ? 2 : 8;
+
+template <int KP, bool FULL>
 __global__ void __launch_bounds__(256)
 k_rmse_coo(const int32_t *__restrict__ rows, const int32_t *__restrict__ cols,
            const float *__restrict__ vals, int64_t nnz, const float *__restrict__ U,
            const float *__restrict__ V, int32_t k, int64_t n, int64_t m,
            double *__restrict__ partials, int32_t *bad) {
-  constexpr int L = rmse_lanes<KP>();
+  using Dt = Dot<KP, FULL>;
+  constexpr int L = Dt::L, QL = Dt::QL;
   constexpr int RPS = 64 / L;
-  constexpr int Q = KP / 4;
-  constexpr int QL = (Q + L - 1) / L;
+  constexpr int UNR = kCooUnroll<KP>;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int gl = lane % L, grp = lane / L;
+  const Dt dot(gl, k);
+  const uint32_t rowbytes = (uint32_t)k * 4u;
   const int64_t gw = (int64_t)blockIdx.x * kWavesPerGroup + wave;
   const int64_t stride = (int64_t)gridDim.x * kWavesPerGroup * RPS;
-  const int kq = k / 4;
   double acc = 0.0;
-  for (int64_t t = gw * RPS + grp; t - grp < nnz; t += stride) {
-    bool ok = t < nnz;
-    const int64_t e = ok ? t : 0;
-    int64_t i = rows[e], j = cols[e];
-    const float x = vals[e];
-    const bool in = i >= 0 && i < n && j >= 0 && j < m;
-    const bool fin = __builtin_isfinite(x);
-    if (ok && gl == 0 && !(in && fin)) atomicOr(bad, (in ? 0 : 1) | (fin ? 0 : 2));
-    ok = ok && in && fin;
-    if (!in) i = j = 0;
-    const float4 *up = reinterpret_cast<const float4 *>(U + i * k);
-    const float4 *vp = reinterpret_cast<const float4 *>(V + j * k);
-    float part = 0.0f;
+  int32_t ri[UNR], rj[UNR];
+  float rx[UNR];
+  auto fetch = [&](int64_t t0) {
 #pragma unroll
-    for (int i = 0; i < QL; ++i) {
-      const int q = gl + i * L;
-      if (q < kq) {
-        const float4 a = up[q], c = vp[q];
-        part = fmaf(a.x, c.x, part);
-        part = fmaf(a.y, c.y, part);
-        part = fmaf(a.z, c.z, part);
-        part = fmaf(a.w, c.w, part);
-      }
+    for (int u = 0; u < UNR; ++u) {
+      const int64_t t = t0 + u * stride + grp;
+      const int64_t e = t < nnz ? t : 0;
+      ri[u] = rows[e];
+      rj[u] = cols[e];
+      rx[u] = vals[e];
     }
-    part += dpp_mov<0xB1>(part);
-    if constexpr (L > 2) part += dpp_mov<0x4E>(part);
-    if constexpr (L > 4) part += dpp_mov<0x141>(part);
-    if constexpr (L > 8) part += dpp_mov<0x140>(part);
-    const float d = (ok && gl == 0) ? x - part : 0.0f;
-    acc = fma((double)d, (double)d, acc);
+  };
+  int64_t t0 = gw * RPS;
+  if (t0 < nnz) fetch(t0);
+  for (; t0 < nnz; t0 += UNR * stride) {
+    float4 ua[UNR][QL], va[UNR][QL];
+    float x[UNR];
+    bool ok[UNR];
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+      const bool live = t0 + u * stride + grp < nnz;
+      const bool in = ri[u] >= 0 && ri[u] < n && rj[u] >= 0 && rj[u] < m;
+      const bool fin = __builtin_isfinite(rx[u]);
+      if (live && gl == 0 && !(in && fin)) atomicOr(bad, (in ? 0 : 1) | (fin ? 0 : 2));
+      ok[u] = live && in && fin;
+      x[u] = rx[u];
+      dot.load(ua[u], row_ptr(U, in ? (uint32_t)ri[u] : 0u, rowbytes));
+      dot.load(va[u], row_ptr(V, in ? (uint32_t)rj[u] : 0u, rowbytes));
+    }
+    fetch(t0 + UNR * stride);
+#pragma unroll
+    for (int u = 0; u < UNR; ++u) {
+      float d = dot.error(x[u], ua[u], va[u]);
+      d = ok[u] ? d : 0.0f;
+      acc = fma((double)d, (double)d, acc);
+    }
   }
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+  acc = wave_sum<L>(acc);
   if (lane == 0) partials[gw] = acc;
 }
 
@@ -277,23 +312,26 @@ __global__ void k_zero(double *x, int64_t count) {
 // block starts and column-blocks in LDS gives the block of each rating (a
 // lane group steps its block forward as its ratings cross block starts), so
 // no block boundary waits for memory.  Used when the rows and the tables
-// fit in LDS.
+// fit in LDS.  Bound by the vector cache, which returns the v rows (256
+// bytes per rating at k = 64): 1.30 ms for 100M ratings, of which 0.92
+// remain without those loads, while the LDS reads cost nothing on top.
 constexpr int kLdsWaves = 16;
 
-template <int KP>
+template <int KP, bool FULL>
 __global__ void __launch_bounds__(1024)
 k_rmse_lds(const uint2 *__restrict__ rec, const int64_t *__restrict__ wblock_ptr,
            const float *__restrict__ U, const float *__restrict__ V, Grid G, int32_t k,
            double *__restrict__ partials) {
-  const int32_t p = G.p;
-  constexpr int L = rmse_lanes<KP>();
+  using Dt = Dot<KP, FULL>;
+  constexpr int L = Dt::L, QL = Dt::QL;
   constexpr int RPS = 64 / L;
-  constexpr int Q = KP / 4;
-  constexpr int QL = (Q + L - 1) / L;
-  constexpr int UNR = rmse_unroll<KP>();
+  constexpr int UNR = rmse_unroll_lds<KP>();
+  const int32_t p = G.p;
   extern __shared__ float4 us[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int gl = lane % L, grp = lane / L;
+  const int grp = lane / L;
+  const Dt dot(lane % L, k);
+  const uint32_t rowbytes = (uint32_t)k * 4u;
   const int b = blockIdx.x;
   const int64_t r0 = G.row_start(b);
   const uint32_t rows_b = (uint32_t)(G.row_start(b + 1) - r0);
@@ -334,70 +372,61 @@ k_rmse_lds(const uint2 *__restrict__ rec, const int64_t *__restrict__ wblock_ptr
     int32_t nb = bnd[sg + 1];  // start of the block after it
     int2 ct = ctab[sg];
     const uint2 *rb = rec + W0;
-    // records of the next iteration are loaded one iteration ahead, so the
-    // factor-row loads never wait for a record load
+    // The records of an iteration are loaded two iterations ahead and turned
+    // into row addresses one iteration ahead, while the rows of the current
+    // one are on their way, so no load waits for another.
     uint2 rn[UNR];
-#pragma unroll
-    for (int u = 0; u < UNR; ++u) {
-      const int32_t t = tb + u * RPS + grp;
-      rn[u] = rb[t < te ? t : tb];
-    }
-    for (int32_t t0 = tb; t0 < te; t0 += RPS * UNR) {
-      float4 a[UNR][QL], c[UNR][QL];
-      float x[UNR];
-      bool ok[UNR];
-      uint2 r[UNR];
-#pragma unroll
-      for (int u = 0; u < UNR; ++u) {
-        r[u] = rn[u];
-        const int32_t t = t0 + RPS * UNR + u * RPS + grp;
-        rn[u] = rb[t < te ? t : tb];
-      }
+    const char *vp[UNR];
+    uint32_t uo[UNR];
+    float xn[UNR];
+    auto fetch = [&](int32_t t0) {
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
         const int32_t t = t0 + u * RPS + grp;
-        ok[u] = t < te;
-        // step to the block of rating t (past empty blocks); t < T = bnd[p]
-        while (ok[u] && t >= nb) {
-          ++sg;
-          nb = bnd[sg + 1];
-          ct = ctab[sg];
-        }
-        x[u] = __uint_as_float(r[u].y);
-        const uint32_t row = min(r[u].x & kRowMask, rmax);
-        const uint32_t col = min((r[u].x >> kColShift) & kColMask, (uint32_t)ct.y);
-        const float4 *vp = reinterpret_cast<const float4 *>(V + ((int64_t)ct.x + col) * k);
-#pragma unroll
-        for (int i = 0; i < QL; ++i) {
-          // branch-free: slices past k read slice 0 and are zeroed after
-          const int q = gl + i * L;
-          const bool in = q < kq;
-          const int qc = in ? q : 0;
-          a[u][i] = us[row * kq + qc];
-          c[u][i] = vp[qc];
-          if (!in) a[u][i] = make_float4(0.f, 0.f, 0.f, 0.f);
-        }
+        rn[u] = rb[t < te ? t : tb];
       }
+    };
+    auto decode = [&](int32_t t0) {
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
-        float part = 0.0f;
-#pragma unroll
-        for (int i = 0; i < QL; ++i) {
-          part = fmaf(a[u][i].x, c[u][i].x, part);
-          part = fmaf(a[u][i].y, c[u][i].y, part);
-          part = fmaf(a[u][i].z, c[u][i].z, part);
-          part = fmaf(a[u][i].w, c[u][i].w, part);
+        const int32_t t = t0 + u * RPS + grp;
+        // step to the block of rating t (past empty blocks); te <= bnd[p]
+        if (t < te && t >= nb) {
+          do {
+            ++sg;
+            nb = bnd[sg + 1];
+          } while (t >= nb);
+          ct = ctab[sg];
         }
-        part += dpp_mov<0xB1>(part);
-        if constexpr (L > 2) part += dpp_mov<0x4E>(part);
-        if constexpr (L > 4) part += dpp_mov<0x141>(part);
-        if constexpr (L > 8) part += dpp_mov<0x140>(part);
-        const float d = (ok[u] && gl == 0) ? x[u] - part : 0.0f;
+        xn[u] = __uint_as_float(rn[u].y);
+        uo[u] = min(rn[u].x & kRowMask, rmax) * rowbytes;
+        vp[u] = row_ptr(V, (uint32_t)ct.x + min((rn[u].x >> kColShift) & kColMask, (uint32_t)ct.y),
+                        rowbytes);
+      }
+    };
+    fetch(tb);
+    decode(tb);
+    fetch(tb + RPS * UNR);
+    for (int32_t t0 = tb; t0 < te; t0 += RPS * UNR) {
+      float4 ua[UNR][QL], va[UNR][QL];
+      float x[UNR];
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) {
+        dot.load(va[u], vp[u]);
+        dot.load(ua[u], reinterpret_cast<const char *>(us) + uo[u]);
+        x[u] = xn[u];
+      }
+      decode(t0 + RPS * UNR);
+      fetch(t0 + 2 * RPS * UNR);
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) {
+        float d = dot.error(x[u], ua[u], va[u]);
+        d = t0 + u * RPS + grp < te ? d : 0.0f;
         acc = fma((double)d, (double)d, acc);
       }
     }
   }
-  for (int off = 32; off > 0; off >>= 1) acc += __shfl_xor(acc, off);
+  acc = wave_sum<L>(acc);
   if (lane == 0) partials[(int64_t)b * kLdsWaves + wave] = acc;
 }
 
@@ -435,7 +464,7 @@ size_t rmse_partials_count(int32_t p) {
 }
 
 namespace {
-template <int KP>
+template <int KP, bool FULL>
 hipError_t launch_rmse_kp(const uint2 *rec, const int64_t *wblock_ptr, const float *U,
                           const float *V, const Grid &G, int64_t rows_max, int32_t k,
                           double *partials, size_t lds_limit, int64_t *count,
@@ -446,22 +475,41 @@ hipError_t launch_rmse_kp(const uint2 *rec, const int64_t *wblock_ptr, const flo
   if (lds <= lds_limit) {
     static bool attr_set = false;
     if (!attr_set) {
-      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_rmse_lds<KP>),
+      hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&k_rmse_lds<KP, FULL>),
                                          hipFuncAttributeMaxDynamicSharedMemorySize,
                                          (int)lds_limit);
       if (e != hipSuccess) return e;
       attr_set = true;
     }
-    hipLaunchKernelGGL(k_rmse_lds<KP>, dim3((unsigned)p), dim3(64 * kLdsWaves), lds, stream, rec,
-                       wblock_ptr, U, V, G, k, partials);
+    hipLaunchKernelGGL((k_rmse_lds<KP, FULL>), dim3((unsigned)p), dim3(64 * kLdsWaves), lds, stream,
+                       rec, wblock_ptr, U, V, G, k, partials);
     *count = (int64_t)p * kLdsWaves;
   } else {
     const int64_t groups = (int64_t)p * ((p + kRmseColGroup - 1) / kRmseColGroup);
-    hipLaunchKernelGGL(k_rmse_partial<KP>, dim3((unsigned)groups), dim3(256), 0, stream,
+    hipLaunchKernelGGL((k_rmse_partial<KP, FULL>), dim3((unsigned)groups), dim3(256), 0, stream,
                        rec, wblock_ptr, U, V, G, k, partials);
     *count = groups * kWavesPerGroup;
   }
   return hipGetLastError();
+}
+
+// Calls f with the kernels' template arguments for width k.
+template <class F>
+hipError_t with_width(int32_t k, F &&f) {
+  int kp = 16;
+  while (kp < k) kp <<= 1;
+  auto full = [&](auto w) {
+    constexpr int KP = decltype(w)::value;
+    return k == KP ? f(w, std::true_type{}) : f(w, std::false_type{});
+  };
+  switch (kp) {
+    case 16: return f(std::integral_constant<int, 16>{}, std::true_type{});
+    case 32: return f(std::integral_constant<int, 32>{}, std::true_type{});
+    case 64: return full(std::integral_constant<int, 64>{});
+    case 128: return full(std::integral_constant<int, 128>{});
+    case 256: return full(std::integral_constant<int, 256>{});
+    default: return hipErrorInvalidValue;
+  }
 }
 }  // namespace
 
@@ -476,24 +524,13 @@ hipError_t rmse_stratum_add(const uint2 *rec, int64_t rec_origin, const int64_t 
                             int32_t s0, int32_t s1, const float *U, const float *V,
                             const Grid &G, int32_t k, double *partials, hipStream_t stream) {
   const int32_t p = G.p;
-  int kp = 16;
-  while (kp < k) kp <<= 1;
   const dim3 grid((unsigned)((p + kWavesPerGroup - 1) / kWavesPerGroup),
-                  (unsigned)std::min(kRmseStrataGroups, s1 - s0)),
-      block(256);
-#define BGMF_RS(KPV)                                                                            \
-  hipLaunchKernelGGL(k_rmse_stratum<KPV>, grid, block, 0, stream, rec, rec_origin, block_ptr, s0, \
-                     s1, U, V, G, k, partials)
-  switch (kp) {
-    case 16: BGMF_RS(16); break;
-    case 32: BGMF_RS(32); break;
-    case 64: BGMF_RS(64); break;
-    case 128: BGMF_RS(128); break;
-    case 256: BGMF_RS(256); break;
-    default: return hipErrorInvalidValue;
-  }
-#undef BGMF_RS
-  return hipGetLastError();
+                  (unsigned)std::min(kRmseStrataGroups, s1 - s0));
+  return with_width(k, [&](auto w, auto full) {
+    hipLaunchKernelGGL((k_rmse_stratum<decltype(w)::value, decltype(full)::value>), grid, dim3(256),
+                       0, stream, rec, rec_origin, block_ptr, s0, s1, U, V, G, k, partials);
+    return hipGetLastError();
+  });
 }
 
 hipError_t rmse_stratum_end(const double *partials, int32_t p, int64_t nnz, double *out,
@@ -509,22 +546,14 @@ hipError_t launch_rmse_coo(const int32_t *rows, const int32_t *cols, const float
                            int64_t nnz, const float *U, const float *V, int32_t k, int64_t n,
                            int64_t m, double *partials, double *out, int32_t *bad,
                            hipStream_t stream) {
-  int kp = 16;
-  while (kp < k) kp <<= 1;
-  const dim3 grid(kRmseCooGroups), block(64 * kWavesPerGroup);
   hipLaunchKernelGGL(k_zero_i32, dim3(1), dim3(1), 0, stream, bad);
-#define BGMF_RC(KPV)                                                                           \
-  hipLaunchKernelGGL(k_rmse_coo<KPV>, grid, block, 0, stream, rows, cols, vals, nnz, U, V, k, \
-                     n, m, partials, bad)
-  switch (kp) {
-    case 16: BGMF_RC(16); break;
-    case 32: BGMF_RC(32); break;
-    case 64: BGMF_RC(64); break;
-    case 128: BGMF_RC(128); break;
-    case 256: BGMF_RC(256); break;
-    default: return hipErrorInvalidValue;
-  }
-#undef BGMF_RC
+  hipError_t e = with_width(k, [&](auto w, auto full) {
+    hipLaunchKernelGGL((k_rmse_coo<decltype(w)::value, decltype(full)::value>),
+                       dim3(kRmseCooGroups), dim3(64 * kWavesPerGroup), 0, stream, rows, cols, vals,
+                       nnz, U, V, k, n, m, partials, bad);
+    return hipGetLastError();
+  });
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_rmse_final, dim3(1), dim3(256), 0, stream, partials,
                      (int64_t)rmse_coo_partials_count(), nnz, out);
   return hipGetLastError();
@@ -533,18 +562,11 @@ hipError_t launch_rmse_coo(const int32_t *rows, const int32_t *cols, const float
 hipError_t launch_rmse(const uint2 *rec, const int64_t *wblock_ptr, const float *U,
                        const float *V, const Grid &G, int64_t rows_max, int32_t k, int64_t nnz,
                        double *partials, double *out, size_t lds_limit, hipStream_t stream) {
-  int kp = 16;
-  while (kp < k) kp <<= 1;
   int64_t count = 0;
-  hipError_t e;
-  switch (kp) {
-    case 16: e = launch_rmse_kp<16>(rec, wblock_ptr, U, V, G, rows_max, k, partials, lds_limit, &count, stream); break;
-    case 32: e = launch_rmse_kp<32>(rec, wblock_ptr, U, V, G, rows_max, k, partials, lds_limit, &count, stream); break;
-    case 64: e = launch_rmse_kp<64>(rec, wblock_ptr, U, V, G, rows_max, k, partials, lds_limit, &count, stream); break;
-    case 128: e = launch_rmse_kp<128>(rec, wblock_ptr, U, V, G, rows_max, k, partials, lds_limit, &count, stream); break;
-    case 256: e = launch_rmse_kp<256>(rec, wblock_ptr, U, V, G, rows_max, k, partials, lds_limit, &count, stream); break;
-    default: return hipErrorInvalidValue;
-  }
+  hipError_t e = with_width(k, [&](auto w, auto full) {
+    return launch_rmse_kp<decltype(w)::value, decltype(full)::value>(
+        rec, wblock_ptr, U, V, G, rows_max, k, partials, lds_limit, &count, stream);
+  });
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_rmse_final, dim3(1), dim3(256), 0, stream, partials, count, nnz, out);
   return hipGetLastError();
