@@ -35,10 +35,16 @@ __device__ __forceinline__ int64_t gid() {
 
 // Key of a rating: (slot - q0, local row).  Every rating's slot lies in
 // [q0, q0 + nq); a slot outside it gets the key nq (past every table) and
-// raises the layout error.
+// raises the layout error.  K is 32 bits wide where the key fits (every
+// in-core grid up to p = 1024 with rows in proportion), which halves the
+// sort's key traffic; the scratch this frees holds the finished record of
+// each rating (pay), so the gather after the sort reads one random 8-byte
+// word per rating instead of its column and value.
+template <class K>
 __global__ void k_make_keys(const int32_t *__restrict__ rows, const int32_t *__restrict__ cols,
-                            int64_t nnz, Grid G, int rbits, int64_t q0, int64_t nq,
-                            uint64_t *__restrict__ keys, int32_t *__restrict__ idx, int32_t *err) {
+                            const float *__restrict__ vals, int64_t nnz, Grid G, int rbits,
+                            int64_t q0, int64_t nq, K *__restrict__ keys,
+                            int32_t *__restrict__ idx, uint2 *__restrict__ pay, int32_t *err) {
   for (int64_t e = gid(); e < nnz; e += (int64_t)gridDim.x * blockDim.x) {
     const int64_t i = rows[e], j = cols[e];
     const int64_t R = G.row_block(i);
@@ -50,8 +56,12 @@ __global__ void k_make_keys(const int32_t *__restrict__ rows, const int32_t *__r
       atomicOr(err, kErrLayout);
       q = nq;
     }
-    keys[e] = ((uint64_t)q << rbits) | (uint64_t)(i - G.row_start(R));
+    const uint32_t lrow = (uint32_t)(i - G.row_start(R));
+    keys[e] = ((K)q << rbits) | (K)lrow;
     idx[e] = (int32_t)e;
+    if constexpr (sizeof(K) == 4)
+      pay[e] = make_uint2(lrow | ((uint32_t)(j - G.col_start(C)) << kColShift),
+                          __float_as_uint(vals[e]));
   }
 }
 
@@ -163,8 +173,9 @@ hipError_t scan_exclusive(const int64_t *in, int64_t len, int64_t *out, Arena &a
 // Element order inside a tile: index = tile*kTile + i*kThreads + thread, for
 // i = 0..kItems-1.  The histogram and the scatter use the same order.
 
+template <class K>
 __global__ void __launch_bounds__(kThreads)
-k_radix_hist(const uint64_t *__restrict__ keys, int64_t nnz, int shift, int64_t tiles,
+k_radix_hist(const K *__restrict__ keys, int64_t nnz, int shift, int64_t tiles,
              int64_t *__restrict__ counts) {
   __shared__ int hist[kBins];
   hist[threadIdx.x] = 0;
@@ -179,9 +190,10 @@ k_radix_hist(const uint64_t *__restrict__ keys, int64_t nnz, int shift, int64_t 
   counts[(int64_t)threadIdx.x * tiles + blockIdx.x] = hist[threadIdx.x];
 }
 
+template <class K>
 __global__ void __launch_bounds__(kThreads)
-k_radix_scatter(const uint64_t *__restrict__ kin, const int32_t *__restrict__ vin,
-                uint64_t *__restrict__ kout, int32_t *__restrict__ vout, int64_t nnz, int shift,
+k_radix_scatter(const K *__restrict__ kin, const int32_t *__restrict__ vin,
+                K *__restrict__ kout, int32_t *__restrict__ vout, int64_t nnz, int shift,
                 int64_t tiles, const int64_t *__restrict__ offsets, int32_t *err) {
   __shared__ int cnt[kWavesPerGroup][kBins];
   __shared__ int run[kBins];
@@ -196,7 +208,7 @@ k_radix_scatter(const uint64_t *__restrict__ kin, const int32_t *__restrict__ vi
   for (int i = 0; i < kItems; ++i) {
     const int64_t e = base + (int64_t)i * kThreads;
     const bool valid = e < nnz;
-    uint64_t key = valid ? kin[e] : 0;
+    const K key = valid ? kin[e] : 0;
     const int32_t val = valid ? vin[e] : 0;
     const int digit = (int)((key >> shift) & (kBins - 1));
     // lanes holding the same digit
@@ -241,15 +253,16 @@ k_radix_scatter(const uint64_t *__restrict__ kin, const int32_t *__restrict__ vi
 // slot instead of one per rating (counts start at 0; the arithmetic wraps
 // modulo 2^64 and ends at end - start).  Keys of out-of-range slots sort
 // last and raise the layout error.
-__global__ void k_slot_count(const uint64_t *__restrict__ keys, int64_t nnz, int rbits,
+template <class K>
+__global__ void k_slot_count(const K *__restrict__ keys, int64_t nnz, int rbits,
                              int64_t slots, unsigned long long *__restrict__ count, int32_t *err) {
   for (int64_t t = gid(); t < nnz; t += (int64_t)gridDim.x * blockDim.x) {
-    const uint64_t q = keys[t] >> rbits;
+    const uint64_t q = (uint64_t)keys[t] >> rbits;
     if (q >= (uint64_t)slots) {
       atomicOr(err, kErrLayout);
       continue;
     }
-    const uint64_t qp = t > 0 ? keys[t - 1] >> rbits : ~0ull;
+    const uint64_t qp = t > 0 ? (uint64_t)keys[t - 1] >> rbits : ~0ull;
     if (q != qp) {
       atomicAdd(&count[q], 0ull - (unsigned long long)t);
       if (qp < (uint64_t)slots) atomicAdd(&count[qp], (unsigned long long)t);
@@ -268,12 +281,16 @@ __global__ void k_transpose(const int64_t *__restrict__ count, int32_t p,
   }
 }
 
-__global__ void k_gather(const uint64_t *__restrict__ skeys, const int32_t *__restrict__ perm,
+// The records come from pay (32-bit keys, see k_make_keys) or from the
+// input's columns and values.
+template <class K>
+__global__ void k_gather(const K *__restrict__ skeys, const int32_t *__restrict__ perm,
                          const int32_t *__restrict__ cols, const float *__restrict__ vals,
-                         int64_t nnz, Grid G, int rbits, int64_t q0, int64_t nq,
+                         const uint2 *__restrict__ pay, int64_t nnz, Grid G, int rbits, int64_t q0, int64_t nq,
                          const int64_t *__restrict__ block_ptr,
                          const int64_t *__restrict__ wblock_ptr, bool stratum_major,
                          uint2 *__restrict__ rec, uint8_t *__restrict__ nofold, int32_t *err) {
+  constexpr bool kPay = sizeof(K) == 4;
   const uint64_t rmask = (rbits == 0) ? 0ull : ((1ull << rbits) - 1ull);
   const int lane = threadIdx.x & 63;
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -285,11 +302,25 @@ __global__ void k_gather(const uint64_t *__restrict__ skeys, const int32_t *__re
     const bool in = t < nnz;
     const int32_t e = in ? perm[t] : 0;
     const bool e_ok = in && e >= 0 && e < nnz;
-    const int32_t j = e_ok ? cols[e] : -1;
+    // column of the rating: the local one (of the same block where two are
+    // compared) with pay
+    uint2 r = make_uint2(0u, 0u);
+    int32_t j = -1;
+    auto column = [&](int32_t x) {
+      return kPay ? (int32_t)(pay[x].x >> kColShift) : cols[x];
+    };
+    if (e_ok) {
+      if constexpr (kPay) {
+        r = pay[e];
+        j = (int32_t)(r.x >> kColShift);
+      } else {
+        j = cols[e];
+      }
+    }
     int32_t jprev = __shfl_up(j, 1);
     if (lane == 0 && in && t > 0) {
       const int32_t ep = perm[t - 1];
-      jprev = (ep >= 0 && ep < nnz) ? cols[ep] : -1;
+      jprev = (ep >= 0 && ep < nnz) ? column(ep) : -1;
     }
     if (!in) continue;
     if (!e_ok) {
@@ -309,16 +340,19 @@ __global__ void k_gather(const uint64_t *__restrict__ skeys, const int32_t *__re
     // and row (rows ascend inside a block, so equal rows are adjacent), and
     // a column that differs from the previous rating's in the same block
     // means more than one column
-    if (t > 0 && (skeys[t - 1] >> rbits) == (key >> rbits) &&
-        (skeys[t - 1] == key || jprev != j))
+    const uint64_t kprev = t > 0 ? (uint64_t)skeys[t - 1] : 0ull;
+    if (t > 0 && (kprev >> rbits) == (key >> rbits) && (kprev == key || jprev != j))
       nofold[q] = 1;
     const int64_t s = q / G.p, b = q - s * G.p;
-    const int64_t C = (b + s) % G.p;
-    const uint32_t lcol = (uint32_t)(j - G.col_start(C));
+    if constexpr (!kPay) {
+      const int64_t C = (b + s) % G.p;
+      r = make_uint2(lrow | ((uint32_t)(j - G.col_start(C)) << kColShift),
+                     __float_as_uint(vals[e]));
+    }
     const int64_t beg = block_ptr[ql];
     const int64_t pos = stratum_major ? t : wblock_ptr[b * G.p + s] + (t - beg);
     if (pos >= 0 && pos < nnz && t >= beg && t < block_ptr[ql + 1])
-      rec[pos] = make_uint2(lrow | (lcol << kColShift), __float_as_uint(vals[e]));
+      rec[pos] = r;
     else
       atomicOr(err, kErrLayout);
   }
@@ -464,53 +498,51 @@ size_t bucket_scratch_bytes(int64_t nnz, int64_t nq) {
   return b;
 }
 
-hipError_t bucket(const int32_t *rows, const int32_t *cols, const float *vals, int64_t nnz,
-                  const Grid &G, int64_t rows_max, int64_t q0, int64_t nq, bool stratum_major,
-                  void *scratch, size_t scratch_bytes, const BucketOut &out, int32_t *err,
-                  hipStream_t st) {
+namespace {
+template <class K>
+hipError_t bucket_keys(const int32_t *rows, const int32_t *cols, const float *vals, int64_t nnz,
+                       const Grid &G, int rbits, int total_bits, int64_t q0, int64_t nq,
+                       bool stratum_major, void *scratch, size_t scratch_bytes,
+                       const BucketOut &out, int32_t *err, hipStream_t st) {
   const int32_t p = G.p;
   const int64_t slots = nq;
-  if (!stratum_major && (q0 != 0 || nq != (int64_t)p * p)) return hipErrorInvalidValue;
-  const int rbits = bits_for((uint64_t)(rows_max < 1 ? 1 : rows_max));
-  const int qbits = bits_for((uint64_t)slots + 1);
-  const int total_bits = rbits + qbits;
   const int passes = total_bits <= 0 ? 1 : (total_bits + 7) / 8;
   const int64_t tiles = (nnz + kTile - 1) / kTile;
 
   Arena ar{static_cast<char *>(scratch), scratch_bytes, 0};
-  uint64_t *k0 = ar.take<uint64_t>((size_t)nnz), *k1 = ar.take<uint64_t>((size_t)nnz);
+  K *k0 = ar.take<K>((size_t)nnz), *k1 = ar.take<K>((size_t)nnz);
+  uint2 *pay = sizeof(K) == 4 ? ar.take<uint2>((size_t)nnz) : nullptr;
   int32_t *v0 = ar.take<int32_t>((size_t)nnz), *v1 = ar.take<int32_t>((size_t)nnz);
   int64_t *counts = ar.take<int64_t>((size_t)kBins * tiles);
   int64_t *offsets = ar.take<int64_t>((size_t)kBins * tiles + 1);
   int64_t *slot_count = ar.take<int64_t>((size_t)slots + 1);
   int64_t *slot_count_w = ar.take<int64_t>((size_t)slots + 1);
-  if (!k0 || !k1 || !v0 || !v1 || !counts || !offsets || !slot_count || !slot_count_w)
+  if (!k0 || !k1 || (sizeof(K) == 4 && !pay) || !v0 || !v1 || !counts || !offsets ||
+      !slot_count || !slot_count_w)
     return hipErrorOutOfMemory;
 
   const int g = grid_for(nnz, kThreads);
-  hipLaunchKernelGGL(k_make_keys, dim3(g), dim3(kThreads), 0, st, rows, cols, nnz, G, rbits, q0,
-                     nq, k0, v0, err);
-  uint64_t *kin = k0, *kout = k1;
+  hipLaunchKernelGGL(k_make_keys<K>, dim3(g), dim3(kThreads), 0, st, rows, cols, vals, nnz, G,
+                     rbits, q0, nq, k0, v0, pay, err);
+  K *kin = k0, *kout = k1;
   int32_t *vin = v0, *vout = v1;
   for (int pass = 0; pass < passes; ++pass) {
     const int shift = pass * 8;
-    hipLaunchKernelGGL(k_radix_hist, dim3((unsigned)tiles), dim3(kThreads), 0, st, kin, nnz,
+    if (pass == passes - 1) vout = out.perm;  // the sorted positions are perm
+    hipLaunchKernelGGL(k_radix_hist<K>, dim3((unsigned)tiles), dim3(kThreads), 0, st, kin, nnz,
                        shift, tiles, counts);
     Arena scan_ar = ar;
     hipError_t e = scan_exclusive(counts, (int64_t)kBins * tiles, offsets, scan_ar, st);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_radix_scatter, dim3((unsigned)tiles), dim3(kThreads), 0, st, kin, vin,
+    hipLaunchKernelGGL(k_radix_scatter<K>, dim3((unsigned)tiles), dim3(kThreads), 0, st, kin, vin,
                        kout, vout, nnz, shift, tiles, offsets, err);
-    uint64_t *tk = kin; kin = kout; kout = tk;
+    K *tk = kin; kin = kout; kout = tk;
     int32_t *tv = vin; vin = vout; vout = tv;
   }
   // kin / vin hold the sorted keys and input positions
-  hipError_t e = hipMemcpyAsync(out.perm, vin, (size_t)nnz * sizeof(int32_t),
-                                hipMemcpyDeviceToDevice, st);
+  hipError_t e = hipMemsetAsync(slot_count, 0, (size_t)(slots + 1) * sizeof(int64_t), st);
   if (e != hipSuccess) return e;
-  e = hipMemsetAsync(slot_count, 0, (size_t)(slots + 1) * sizeof(int64_t), st);
-  if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_slot_count, dim3(g), dim3(kThreads), 0, st, kin, nnz, rbits, slots,
+  hipLaunchKernelGGL(k_slot_count<K>, dim3(g), dim3(kThreads), 0, st, kin, nnz, rbits, slots,
                      reinterpret_cast<unsigned long long *>(slot_count), err);
   {
     Arena scan_ar = ar;
@@ -526,10 +558,23 @@ hipError_t bucket(const int32_t *rows, const int32_t *cols, const float *vals, i
   }
   hipLaunchKernelGGL(k_fill_rec, dim3(1), dim3(kThreads), 0, st, out.rec + nnz,
                      (int64_t)kRecPad);
-  hipLaunchKernelGGL(k_gather, dim3(g), dim3(kThreads), 0, st, kin, vin, cols, vals, nnz, G,
-                     rbits, q0, nq, out.block_ptr, out.wblock_ptr, stratum_major, out.rec,
+  hipLaunchKernelGGL(k_gather<K>, dim3(g), dim3(kThreads), 0, st, kin, vin, cols, vals, pay, nnz,
+                     G, rbits, q0, nq, out.block_ptr, out.wblock_ptr, stratum_major, out.rec,
                      out.nofold, err);
   return hipGetLastError();
+}
+}  // namespace
+
+hipError_t bucket(const int32_t *rows, const int32_t *cols, const float *vals, int64_t nnz,
+                  const Grid &G, int64_t rows_max, int64_t q0, int64_t nq, bool stratum_major,
+                  void *scratch, size_t scratch_bytes, const BucketOut &out, int32_t *err,
+                  hipStream_t st) {
+  if (!stratum_major && (q0 != 0 || nq != (int64_t)G.p * G.p)) return hipErrorInvalidValue;
+  const int rbits = bits_for((uint64_t)(rows_max < 1 ? 1 : rows_max));
+  const int total_bits = rbits + bits_for((uint64_t)nq + 1);
+  auto run = total_bits <= 32 ? bucket_keys<uint32_t> : bucket_keys<uint64_t>;
+  return run(rows, cols, vals, nnz, G, rbits, total_bits, q0, nq, stratum_major, scratch,
+             scratch_bytes, out, err, st);
 }
 
 }  // namespace bgmfk
