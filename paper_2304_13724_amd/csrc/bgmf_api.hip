@@ -10,6 +10,7 @@
 #include <cstring>
 #include <new>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include <rocprofiler-sdk-roctx/roctx.h>
@@ -184,6 +185,70 @@ int check_device_error(bgmf_t *h) {
 int sync_checked(bgmf_t *h) {
   HIP_TRY(h, hipStreamSynchronize(h->stream));
   return check_device_error(h);
+}
+
+// Host check of nnz ratings against the matrix: returns the first rating that
+// lies outside it or has a non-finite value, or nnz.  Without a branch per
+// rating the inner loop is vector code, bound by one core's memory rate, and
+// from two parts up a few threads share it (10M ratings on an 8-core host:
+// 10.5 ms with a branch per rating, 9.5 without, 1.3 on eight threads; 1M:
+// 0.72, 0.43 and 0.33 on two).
+constexpr int64_t kCheckPart = 1 << 19;
+constexpr int64_t kCheckThreads = 8;
+
+int64_t check_part(const int32_t *rows, const int32_t *cols, const float *vals, int64_t e0,
+                   int64_t e1, int64_t n, int64_t m) {
+  const uint32_t nu = (uint32_t)n, mu = (uint32_t)m;  // both below 2^31
+  for (int64_t a = e0; a < e1; a += 4096) {
+    const int64_t z = std::min<int64_t>(a + 4096, e1);
+    uint32_t bad = 0;
+    for (int64_t e = a; e < z; ++e) {
+      uint32_t bits;
+      std::memcpy(&bits, vals + e, sizeof bits);
+      bad |= (uint32_t)((uint32_t)rows[e] >= nu) | (uint32_t)((uint32_t)cols[e] >= mu) |
+             (uint32_t)((bits & 0x7F800000u) == 0x7F800000u);
+    }
+    if (!bad) continue;
+    for (int64_t e = a; e < z; ++e)
+      if ((uint32_t)rows[e] >= nu || (uint32_t)cols[e] >= mu || !std::isfinite(vals[e])) return e;
+  }
+  return e1;
+}
+
+int64_t first_bad_rating(const int32_t *rows, const int32_t *cols, const float *vals, int64_t nnz,
+                         int64_t n, int64_t m) {
+  const int64_t parts = std::min<int64_t>(
+      {nnz / kCheckPart, kCheckThreads, (int64_t)std::max(1u, std::thread::hardware_concurrency())});
+  if (parts < 2) return check_part(rows, cols, vals, 0, nnz, n, m);
+  int64_t from[kCheckThreads + 1], bad[kCheckThreads];
+  for (int64_t i = 0; i <= parts; ++i) from[i] = nnz / parts * i + std::min(i, nnz % parts);
+  auto part = [&](int64_t i) {
+    bad[i] = check_part(rows, cols, vals, from[i], from[i + 1], n, m);
+  };
+  std::vector<std::thread> threads;
+  int64_t started = 1;  // part 0 is this thread's
+  try {
+    threads.reserve((size_t)parts - 1);
+    for (; started < parts; ++started) threads.emplace_back(part, started);
+  } catch (...) {  // no more threads or memory: the rest is done here
+  }
+  part(0);
+  for (int64_t i = started; i < parts; ++i) part(i);
+  for (auto &t : threads) t.join();
+  for (int64_t i = 0; i < parts; ++i)
+    if (bad[i] < from[i + 1]) return bad[i];
+  return nnz;
+}
+
+// The check's error, if any.
+int check_ratings(bgmf_t *h, const int32_t *rows, const int32_t *cols, const float *vals,
+                  int64_t nnz) {
+  const int64_t e = first_bad_rating(rows, cols, vals, nnz, h->n, h->m);
+  if (e == nnz) return BGMF_OK;
+  if (rows[e] < 0 || rows[e] >= h->n || cols[e] < 0 || cols[e] >= h->m)
+    return fail(h, BGMF_E_RANGE, "rating %lld at (%d, %d) is outside the %lld x %lld matrix",
+                (long long)e, rows[e], cols[e], (long long)h->n, (long long)h->m);
+  return fail(h, BGMF_E_NONFINITE, "rating %lld has a non-finite value", (long long)e);
 }
 
 Grid grid_of(const bgmf_t *h) {
@@ -894,12 +959,9 @@ int bgmf_load_coo(bgmf_t *h, const int32_t *rows, const int32_t *cols, const flo
   if (!rows || !cols || !vals) return fail(h, BGMF_E_ARG, "bgmf_load_coo: null pointer");
   if (nnz < 1 || nnz >= (1ll << 31))
     return fail(h, BGMF_E_ARG, "nnz must be in [1, 2^31): %lld", (long long)nnz);
-  for (int64_t e = 0; e < nnz; ++e) {
-    if (rows[e] < 0 || rows[e] >= h->n || cols[e] < 0 || cols[e] >= h->m)
-      return fail(h, BGMF_E_RANGE, "rating %lld at (%d, %d) is outside the %lld x %lld matrix",
-                  (long long)e, rows[e], cols[e], (long long)h->n, (long long)h->m);
-    if (!std::isfinite(vals[e]))
-      return fail(h, BGMF_E_NONFINITE, "rating %lld has a non-finite value", (long long)e);
+  {
+    const int rc = check_ratings(h, rows, cols, vals, nnz);
+    if (rc != BGMF_OK) return rc;
   }
   HIP_TRY(h, hipStreamSynchronize(h->stream));
   free_layout(h);
@@ -1308,12 +1370,9 @@ int bgmf_rmse_coo(bgmf_t *h, const int32_t *rows, const int32_t *cols, const flo
   if (nnz < 1 || nnz >= (1ll << 31))
     return fail(h, BGMF_E_ARG, "nnz must be in [1, 2^31): %lld", (long long)nnz);
   if (!h->factors_set) return fail(h, BGMF_E_STATE, "bgmf_rmse_coo: factors not set");
-  for (int64_t e = 0; e < nnz; ++e) {
-    if (rows[e] < 0 || rows[e] >= h->n || cols[e] < 0 || cols[e] >= h->m)
-      return fail(h, BGMF_E_RANGE, "rating %lld at (%d, %d) is outside the %lld x %lld matrix",
-                  (long long)e, rows[e], cols[e], (long long)h->n, (long long)h->m);
-    if (!std::isfinite(vals[e]))
-      return fail(h, BGMF_E_NONFINITE, "rating %lld has a non-finite value", (long long)e);
+  {
+    const int rc = check_ratings(h, rows, cols, vals, nnz);
+    if (rc != BGMF_OK) return rc;
   }
   int32_t *d_rows = nullptr, *d_cols = nullptr;
   float *d_vals = nullptr;
