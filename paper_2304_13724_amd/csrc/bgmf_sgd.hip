@@ -805,9 +805,10 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
   constexpr int VPOL = COH ? kCoherent : 0;
   // Shortest run swept as one, and shortest block in which runs are looked
   // for.  Entering and leaving a run each wait for its first rows (about
-  // 1 us together, what 32 ratings gain): runs from 16 up take 111.8 ms per
-  // epoch of 100M ratings at k = 128, p = 2048, from 24 up 110.3 ms, from 32
-  // up 109.0 ms (and 116.8, 117.1, 117.1 ms at 20M ratings, k = 64, p = 4096).
+  // 1 us together, what 32 ratings gain): runs from 16 up take 107.2 ms per
+  // epoch of 100M ratings at k = 128, p = 2048, from 24 up 106.3 ms, from 32
+  // up 106.1 ms (and 115.6, 116.6, 116.3 ms at 20M ratings, k = 64, p = 4096;
+  // without runs 120.0 and 165.1 ms).
   constexpr int kRunMin = 32;
   constexpr int kRunBlock = 48;
   constexpr int kRunRow = 1, kRunCol = 2;
@@ -868,11 +869,18 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
 
     float ring[D][NV], vring[D][NV];
     uint32_t ringrow[D];
-    uint2 Wn1 = make_uint2(0u, 0u);
-    auto open = [&](int32_t t) {
-      t0 = t;
-      decode(rp[t + (lane >= CH ? lane - CH : 0)], t);
-      Wn1 = rp[t + lane];  // window of chunk t + CH
+    // raw records of the current window and of the next chunk's
+    uint2 Wc = make_uint2(0u, 0u), Wn1 = make_uint2(0u, 0u);
+    auto open = [&]() {
+      t0 = 0;
+      Wc = rp[lane >= CH ? lane - CH : 0];
+      decode(Wc, 0);
+      Wn1 = rp[lane];  // window of chunk CH
+    };
+    auto advance = [&](int32_t c, uint2 Wn2) {  // to the window of chunk c
+      Wc = Wn1;
+      decode(Wc, c);
+      Wn1 = Wn2;
     };
     auto prime = [&]() {
 #pragma unroll
@@ -884,7 +892,7 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
     // blocks in which runs are looked for (see below)
     const bool runs = !COH && len >= kRunBlock;
     if (len > 0) {
-      open(0);
+      open();
       if (!runs) prime();
     }
     if (s > P.s_begin) {
@@ -921,8 +929,9 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
         const uint64_t cols = __builtin_amdgcn_ballot_w64(wcol == rl(wcol, CH));
         return (cols & kAll) == kAll ? kRunCol : 0;
       };
-      // Sweeps the run that starts at t (whose window is decoded); returns
-      // the first rating after it, or t if its first chunk has a duplicate.
+      // Sweeps the run that starts at t (whose window is decoded), in whole
+      // chunks; returns the first rating it leaves (whose window is decoded),
+      // or t if its first chunk has a duplicate.
       auto run = [&](int32_t t, bool by_row) -> int32_t {
         const auto rows_of = [&](bool of_v) {  // the block's rows of V or U
           const int64_t base = reinterpret_cast<int64_t>(of_v ? P.V + c0 * k : P.U + r0 * k);
@@ -952,9 +961,7 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
           z[v] = ring[0][v];
           pnz[v] = z[v];  // the first pending store writes rating t's row back unchanged
         }
-        auto step_chunk = [&](auto tail_tag, int32_t c, int32_t count) {
-          constexpr bool TAIL = decltype(tail_tag)::value;
-          const int32_t left = TAIL ? tail_left(count, 0) : CH;
+        auto step_chunk = [&](int32_t c) {
           const uint2 Wn2 = rp[c + CH + lane];
 #pragma unroll
           for (int j = 0; j < CH; ++j) {
@@ -1013,12 +1020,8 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
             poff = ringrow[j];
             x64 = x64n;
             pin();
-            if constexpr (TAIL) {
-              if (j + 1 >= left) break;
-            }
           }
-          decode(Wn1, c + CH);
-          Wn1 = Wn2;
+          advance(c + CH, Wn2);
           wz = by_row ? wcol : wrow;
           // the load of the next chunk's step 0
           const uint64_t hit =
@@ -1031,16 +1034,13 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
               __builtin_amdgcn_ballot_w64((by_row ? wrow : wcol) == own) >> CH;
           return __builtin_amdgcn_readfirstlane(min((int32_t)__builtin_ctzll(~same), len - c));
         };
-        int32_t c = t, left = lead(t);
-        while (left >= CH) {
-          step_chunk(std::false_type{}, c, CH);
+        // full chunks; the run's last ratings (fewer than a chunk) take the
+        // general step, which starts from the window in hand
+        int32_t c = t;
+        do {
+          step_chunk(c);
           c += CH;
-          left = dup ? 0 : lead(c);
-        }
-        if (left > 0) {
-          step_chunk(std::true_type{}, c, left);
-          c += left;
-        }
+        } while (!dup && lead(c) >= CH);
         st_row<NV, 0>(pnz, Zres, doff, poff);
         st_row<NV, 0>(w, Wres, doff, own);
         return c;
@@ -1050,8 +1050,8 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
       // a wave's accesses to one address in order)
       for (int pass = 0; pass < P.passes; ++pass) {
       int32_t seg = 0;
+      if (pass > 0) open();
       while (seg < len) {
-      if (pass > 0 || seg > 0) open(seg);
       if constexpr (!COH) {
         if (runs) {
           const int kind = run_at(seg);
@@ -1059,6 +1059,10 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
           if (next > seg) {
             seg = next;
             continue;
+          }
+          if (seg > 0) {  // a new segment: the ratings before it match no column
+            t0 = seg;
+            decode(Wc, seg);
           }
         }
       }
@@ -1129,8 +1133,7 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
             if (j + 1 >= left) break;  // the block's last rating is done
           }
         }
-        decode(Wn1, c + CH);
-        Wn1 = Wn2;
+        advance(c + CH, Wn2);
       };
       // One float per lane (k <= 64): the same step with the stores of a
       // rating's results deferred into the next rating's reduction and every
@@ -1242,8 +1245,7 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
             if (j + 1 >= left) break;  // the block's last rating is done
           }
         }
-        decode(Wn1, c + CH);
-        Wn1 = Wn2;
+        advance(c + CH, Wn2);
       };
       // full chunks up to the block's end or the start of a run, then the
       // last, partial chunk
