@@ -1,0 +1,83 @@
+"""Loading: the sort's key width (32 bits with the records prepared ahead, 64
+bits without), at the two sides of its limit, in-core and streamed; and the
+host check of the ratings, whose vector loop and threads must still name the
+first bad rating.
+"""
+import numpy as np
+import pytest
+
+import oracle
+
+pytestmark = pytest.mark.gpu
+
+
+def _cuts(n, p):
+    """p blocks: one of 65,536 indices, the others one index each."""
+    return np.r_[0, 65_536 + np.arange(p)].astype(np.int64), 65_536 + p - 1
+
+
+@pytest.mark.parametrize("p", [2, 255, 256])
+@pytest.mark.parametrize("budget", [0, 100_000])
+def test_key_width(p, budget):
+    """Row keys of 16 bits: with p = 255 the slots take 16 more (32 in all),
+    with p = 256 one more."""
+    from paper_2304_13724_amd import bgmf
+    rng = np.random.default_rng(p)
+    rc, n = _cuts(0, p)
+    m = 3 * p + 1
+    cc = np.array([(c * m + p - 1) // p for c in range(p + 1)], dtype=np.int64)
+    nnz = 20_000
+    rows = np.r_[rng.integers(0, n, nnz // 2), rng.integers(65_500, n, nnz - nnz // 2)]
+    cols = rng.integers(0, m, nnz)
+    rows, cols = rows.astype(np.int32), cols.astype(np.int32)
+    vals = rng.integers(1, 6, nnz).astype(np.float32)
+    obp, operm = oracle.bucket_cuts(n, m, p, rc, cc, rows, cols)
+    U = rng.uniform(0, 0.1, (n, 16)).astype(np.float32)
+    V = rng.uniform(0, 0.1, (m, 16)).astype(np.float32)
+    with bgmf.Model(n, m, 16, p) as mdl:
+        mdl.set_cuts(rc, cc)
+        mdl.set_option(bgmf.BGMF_OPT_RATINGS_BUDGET, budget)
+        mdl.set_factors(U, V)
+        try:
+            mdl.load_coo(rows, cols, vals)
+        except bgmf.BgmfError as e:  # two strata of a 2 x 2 grid exceed the budget
+            assert budget and p == 2 and e.code == bgmf.BGMF_E_BUDGET
+            return
+        bp, perm = mdl.get_layout()
+        r = mdl.rmse()
+    assert np.array_equal(bp, obp) and np.array_equal(perm, operm)
+    # the records, through the RMSE that reads them: dots in binary32 (16
+    # terms), squares in binary64
+    d = vals - (U[rows].astype(np.float64) * V[cols]).sum(1)
+    ref = float(np.sqrt((d * d).mean()))
+    assert abs(r - ref) <= 16 * 2.0 ** -24 * ref
+
+
+@pytest.mark.parametrize("nnz", [1, 4_095, 4_097, 1_048_576, 1_600_003])
+def test_first_bad_rating(nnz):
+    from paper_2304_13724_amd import bgmf
+    rng = np.random.default_rng(nnz)
+    n, m = 700, 300
+    rows = rng.integers(0, n, nnz).astype(np.int32)
+    cols = rng.integers(0, m, nnz).astype(np.int32)
+    vals = rng.integers(1, 6, nnz).astype(np.float32)
+    part = nnz // 2
+    spots = sorted({0, nnz - 1, min(4_095, nnz - 1), min(4_096, nnz - 1), part, max(part - 1, 0)})
+    with bgmf.Model(n, m, 16, 4) as mdl:
+        for at in spots:
+            for kind, arr, bad, code in (("row", rows, n, bgmf.BGMF_E_RANGE),
+                                         ("row", rows, -1, bgmf.BGMF_E_RANGE),
+                                         ("col", cols, m, bgmf.BGMF_E_RANGE),
+                                         ("val", vals, np.inf, bgmf.BGMF_E_NONFINITE),
+                                         ("val", vals, np.nan, bgmf.BGMF_E_NONFINITE)):
+                keep = arr[at], vals[-1]
+                arr[at] = bad
+                if at < nnz - 1:
+                    vals[-1] = -np.inf  # a later one is not the one named
+                with pytest.raises(bgmf.BgmfError) as ei:
+                    mdl.load_coo(rows, cols, vals)
+                arr[at] = keep[0]
+                vals[-1] = keep[1]
+                assert ei.value.code == code, kind
+                assert str(ei.value).split("rating ")[1].split(" ")[0] == str(at), kind
+        mdl.load_coo(rows, cols, vals)  # all good again
