@@ -253,8 +253,20 @@ __device__ __forceinline__ float row_sum(float x) {
   return x;
 }
 
-// Sum over the lanes that hold distinct dimensions, returned as a scalar
-// (the value of lane 63).  KPL = lanes holding one copy (16, 32 or 64).
+// The total of a reduction in the lanes that use it.  With 16 lanes per copy
+// the in-row sums leave it in every lane, so the lane read (28 cycles with
+// the operation on its scalar) drops out of the dependency chain: 69.9 to
+// 66.5 ns per rating at k = 16.  Otherwise it is the value of lane 63, read
+// as a scalar; at 32 lanes v_permlane16_swap leaves the same total in every
+// lane and was slower (10M ratings, k = 32: 9.82 to 10.51 ms).
+template <int KPL>
+__device__ __forceinline__ float total(float x) {
+  if constexpr (KPL == 16) return x;
+  else return __uint_as_float(rl(__float_as_uint(x), 63));
+}
+
+// Sum over the lanes that hold distinct dimensions (see total).  KPL = lanes
+// holding one copy (16, 32 or 64).
 // After the in-row sums, row_bcast:15 adds the last lane of each row to the
 // next row and row_bcast:31 adds lane 31 to rows 2 and 3 (lanes without a
 // source add 0), so lane 63 ends with rows 0 + 1 + 2 + 3; the other rows
@@ -265,7 +277,7 @@ __device__ __forceinline__ float lane_total(float x) {
   x = row_sum(x);
   if constexpr (KPL >= 32) x = x + dpp_mov<0x142>(x);  // row_bcast:15
   if constexpr (KPL >= 64) x = x + dpp_mov<0x143>(x);  // row_bcast:31
-  return __uint_as_float((uint32_t)__builtin_amdgcn_readlane(__float_as_int(x), 63));
+  return total<KPL>(x);
 }
 
 // Lane layout shared by both sweeps.  KP: k rounded up to a power of two
@@ -559,7 +571,7 @@ __global__ void __launch_bounds__(256) k_sgd_lds(SgdParams P) {
           pin();
           const uint32_t x64n = rl(__float_as_uint(wx), j + 1);  // the next rating's x
           pin();
-          const float e = __uint_as_float(rl(__float_as_uint(t), 63));
+          const float e = total<KPL>(t);
           pin();
           // LDS address of the column after the next one, computed here;
           // the empty asm keeps the compiler from recomputing it next to
@@ -680,7 +692,7 @@ __global__ void __launch_bounds__(256) k_sgd_lds(SgdParams P) {
 #pragma unroll
           for (int v = 1; v < NV; ++v) B = fmaf(ring[next][v], au[v], B);
           pin();
-          const float e = __uint_as_float(rl(__float_as_uint(t), 63));
+          const float e = total<KPL>(t);
           pin();
           // rating t - 1's u
           st_row<NV, 0>(nu, Ures, doff, prow);
@@ -1008,7 +1020,7 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
             pin();
             if constexpr (KPL >= 64) tt = tt + dpp_mov<0x143>(tt);  // row_bcast:31
             pin();
-            const float e = __uint_as_float(rl(__float_as_uint(tt), 63));
+            const float e = total<KPL>(tt);
             pin();
             const float ae = alpha * e;
 #pragma unroll
@@ -1218,7 +1230,7 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
           pin();
           if constexpr (KPL >= 64) t = t + dpp_mov<0x143>(t);  // row_bcast:31
           pin();
-          const float e = __uint_as_float(rl(__float_as_uint(t), 63));
+          const float e = total<KPL>(t);
           pin();
           // the next rating's v unless it is this rating's column (in the
           // wait states of the lane read)
