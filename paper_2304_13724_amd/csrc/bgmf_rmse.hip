@@ -33,14 +33,20 @@ __device__ __forceinline__ float dpp_mov(float x) {
 // k = 64: 1.58 and 1.56 ms against 1.34).
 template <int KP>
 constexpr int rmse_lanes() { return KP >= 32 ? KP / 16 : KP / 4; }
-// Wave steps whose loads are in flight together.  With U in LDS one
-// workgroup fills a CU, and three steps beat two and one (1.30, 1.34, 1.31
-// ms); without, more waves per CU beat more steps per wave (one step against
-// two: 6.6 against 7.3 ms at 100M ratings, k = 128, p = 2048).
+// Wave steps whose loads are in flight together.  Without U in LDS more
+// waves per CU beat more steps per wave (one step against two: 6.6 against
+// 7.3 ms at 100M ratings, k = 128, p = 2048).
 template <int KP>
 constexpr int rmse_unroll() { return KP >= 64 ? 1 : KP >= 32 ? 2 : 8; }
-template <int KP>
-constexpr int rmse_unroll_lds() { return KP >= 32 ? 3 : 8; }
+// With U in LDS one workgroup of 16 waves fills a CU, which leaves a lane 128
+// registers.  A width that fills its lanes takes three steps (two and one:
+// 1.30, 1.34, 1.31 ms at 100M ratings, k = 64).  A masked width, whose
+// slices have offsets of their own, spills with three; one step is fastest
+// (three, two, one: k = 48 294, 266, 250 us; k = 80 536, 486, 462; k = 144
+// 1042, 943, 880, each 20M ratings).  At k = 16 two of one slice (eight,
+// four, two, one: 58, 57, 54, 72 us at 10M ratings).
+template <int KP, bool FULL>
+constexpr int rmse_unroll_lds() { return KP < 32 ? 2 : FULL ? 3 : 1; }
 
 // Factor rows are addressed in bytes: a 64-bit base plus row * rowbytes is
 // one multiply-add.
@@ -325,7 +331,7 @@ k_rmse_lds(const uint2 *__restrict__ rec, const int64_t *__restrict__ wblock_ptr
   using Dt = Dot<KP, FULL>;
   constexpr int L = Dt::L, QL = Dt::QL;
   constexpr int RPS = 64 / L;
-  constexpr int UNR = rmse_unroll_lds<KP>();
+  constexpr int UNR = rmse_unroll_lds<KP, FULL>();
   const int32_t p = G.p;
   extern __shared__ float4 us[];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
