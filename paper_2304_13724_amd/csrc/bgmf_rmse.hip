@@ -241,9 +241,11 @@ k_rmse_stratum(const uint2 *__restrict__ rec, int64_t rec_origin,
 // of them are in flight: a wave has the rows of kCooUnroll steps outstanding
 // and reads the indices of the steps after them meanwhile (10M ratings,
 // k = 64: 474 us with one step and its indices in turn, 449 with indices
-// ahead, 430 with two steps).
-template <int KP>
-constexpr int kCooUnroll = KP >= 32 ? 2 : 8;
+// ahead, 430 with two steps).  Two steps also at k = 16: eight take 130
+// registers, with which only three quarters of the fixed grid (four waves
+// per SIMD) fit the chip at once, and cost small calls 43.4 us against 40.1
+// (100K ratings; 222 us either way at 10M).
+constexpr int kCooUnroll = 2;
 
 template <int KP, bool FULL>
 __global__ void __launch_bounds__(256)
@@ -254,7 +256,7 @@ k_rmse_coo(const int32_t *__restrict__ rows, const int32_t *__restrict__ cols,
   using Dt = Dot<KP, FULL>;
   constexpr int L = Dt::L, QL = Dt::QL;
   constexpr int RPS = 64 / L;
-  constexpr int UNR = kCooUnroll<KP>;
+  constexpr int UNR = kCooUnroll;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int gl = lane % L, grp = lane / L;
   const Dt dot(gl, k);

@@ -56,3 +56,12 @@ def kernels(tmp_path_factory):
 def test_no_scratch(kernels):
     for name, (res, _) in kernels.items():
         assert res["ScratchSize"] == 0, (name, res)
+
+
+def test_heldout_grid_is_resident(kernels):
+    """The held-out kernel's fixed grid (1024 workgroups of four waves) is
+    four waves on each of 1024 SIMDs: at most 128 registers a lane."""
+    coo = [n for n in kernels if n[0] == "k_rmse_coo"]
+    assert len(coo) == 8
+    for name in coo:
+        assert kernels[name][0]["VGPRs"] <= 128, (name, kernels[name][0])
