@@ -33,11 +33,20 @@ __device__ __forceinline__ float dpp_mov(float x) {
 // k = 64: 1.58 and 1.56 ms against 1.34).
 template <int KP>
 constexpr int rmse_lanes() { return KP >= 32 ? KP / 16 : KP / 4; }
-// Wave steps whose loads are in flight together.  Without U in LDS more
-// waves per CU beat more steps per wave (one step against two: 6.6 against
-// 7.3 ms at 100M ratings, k = 128, p = 2048).
+// Wave steps whose loads are in flight together, without U in LDS.  From
+// KP = 64 up a second step costs waves per SIMD (about 100 registers a lane
+// instead of 60: four or five waves instead of eight), and the launch decides:
+// one of at most few_waves waits for its loads and takes two steps, a larger
+// one gains more from the waves.  In-core pass of 10M ratings, one step
+// against two: k = 64, p = 64 (256 waves) 1.34 and 0.92 ms, p = 400 (11,200)
+// 282 and 266 us, p = 512 (16,384) 342 and 322 (other shapes 415 and 454,
+// 501 and 521), p = 640 (25,600) 322 and 376; k = 128, p = 64 2.52 and 1.80
+// ms, p = 512 712 and 574 us, p = 768 (36,864) 733 and 689, p = 1024 (65,536)
+// 728 and 891.
 template <int KP>
-constexpr int rmse_unroll() { return KP >= 64 ? 1 : KP >= 32 ? 2 : 8; }
+constexpr int64_t few_waves() { return KP == 64 ? 16384 : 40960; }
+template <int KP>
+constexpr int rmse_unroll(bool few) { return KP >= 64 ? (few ? 2 : 1) : KP >= 32 ? 2 : 8; }
 // With U in LDS one workgroup of 16 waves fills a CU, which leaves a lane 128
 // registers.  A width that fills its lanes takes three steps (two and one:
 // 1.30, 1.34, 1.31 ms at 100M ratings, k = 64).  A masked width, whose
@@ -111,8 +120,20 @@ __device__ __forceinline__ double wave_sum(double acc) {
   return acc * (1.0 / L);
 }
 
-// KP: k rounded up to a power of two.
-template <int KP, bool FULL>
+// Keeps a wave step's loads ahead of the arithmetic that follows.  Left to
+// itself the compiler sinks them to their uses, to save registers, and a wave
+// then waits for one or two rows at a time.
+__device__ __forceinline__ void loads_issued() { __builtin_amdgcn_sched_barrier(0); }
+
+// KP: k rounded up to a power of two.  FEW: at most few_waves waves
+// (only from KP = 64 up).
+//
+// The loads are fenced except in the widest kernels of a large launch, whose
+// other waves fill the gaps (k = 128, p = 2048: 2.15 ms without, 2.22 with).
+// Without the fence: 10M ratings, k = 16, p = 32 1.30 against 0.63 ms, p =
+// 256 217 against 161 us; k = 32, p = 64 945 against 562 us; k = 48, p = 512
+// 446 against 397.
+template <int KP, bool FULL, bool FEW>
 __global__ void __launch_bounds__(256)
 k_rmse_partial(const uint2 *__restrict__ rec, const int64_t *__restrict__ wblock_ptr,
                const float *__restrict__ U, const float *__restrict__ V, Grid G, int32_t k,
@@ -120,7 +141,8 @@ k_rmse_partial(const uint2 *__restrict__ rec, const int64_t *__restrict__ wblock
   using Dt = Dot<KP, FULL>;
   constexpr int L = Dt::L, QL = Dt::QL;
   constexpr int RPS = 64 / L;             // ratings per wave step
-  constexpr int UNR = rmse_unroll<KP>();  // wave steps whose loads are in flight together
+  constexpr int UNR = rmse_unroll<KP>(FEW);  // wave steps whose loads are in flight together
+  constexpr bool kFence = KP <= 64 || FEW;
   const int32_t p = G.p;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int grp = lane / L;
@@ -152,17 +174,20 @@ k_rmse_partial(const uint2 *__restrict__ rec, const int64_t *__restrict__ wblock
     for (int32_t t0 = 0; t0 < len; t0 += RPS * UNR) {
       float4 ua[UNR][QL], va[UNR][QL];
       float x[UNR];
+      uint2 r[UNR];
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
-        x[u] = __uint_as_float(rn[u].y);
-        dot.load(ua[u], row_ptr(Ub, min(rn[u].x & kRowMask, rmax), rowbytes));
-        dot.load(va[u], row_ptr(Vb, min((rn[u].x >> kColShift) & kColMask, cmax), rowbytes));
-      }
-#pragma unroll
-      for (int u = 0; u < UNR; ++u) {
+        r[u] = rn[u];
         const int32_t t = t0 + (UNR + u) * RPS + grp;
         rn[u] = rb[t < len ? t : 0];
       }
+#pragma unroll
+      for (int u = 0; u < UNR; ++u) {
+        x[u] = __uint_as_float(r[u].y);
+        dot.load(ua[u], row_ptr(Ub, min(r[u].x & kRowMask, rmax), rowbytes));
+        dot.load(va[u], row_ptr(Vb, min((r[u].x >> kColShift) & kColMask, cmax), rowbytes));
+      }
+      if constexpr (kFence) loads_issued();
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
         float d = dot.error(x[u], ua[u], va[u]);
@@ -179,8 +204,17 @@ k_rmse_partial(const uint2 *__restrict__ rec, const int64_t *__restrict__ wblock
 // wave of row-block b and grid row y adds the squared errors of blocks
 // (b, s), s = s0 + y, s0 + y + gridDim.y, ..., to partials[y p + b] (each
 // partial is owned by one wave per launch, and launches are ordered on the
-// stream).
-template <int KP, bool FULL>
+// stream).  A record and the rows it names are read in the same step.
+//
+// Steps in flight as in k_rmse_partial, FEW from other measurements (ratings
+// streamed, one step and no fence against two fenced: 10M, p = 64, k = 64 4.3
+// and 2.5 ms, k = 128 7.3 and 5.1; p = 1024, k = 128 1.45 and 1.42; 20M, p =
+// 1024, k = 64 2.30 and 2.28; p = 2048, k = 128 2.76 and 3.11; p = 4096, k =
+// 64 3.1 and 4.9).  At k = 16 a fence would hold back the next records' loads
+// (p = 32: 2.8 against 1.8 ms); at k = 32 it pays (1.53 against 1.64).
+constexpr int64_t kStratumFewWaves = 16384;  // 16 p waves in a full launch
+
+template <int KP, bool FULL, bool FEW>
 __global__ void __launch_bounds__(256)
 k_rmse_stratum(const uint2 *__restrict__ rec, int64_t rec_origin,
                const int64_t *__restrict__ block_ptr, int32_t s0, int32_t s1,
@@ -189,7 +223,8 @@ k_rmse_stratum(const uint2 *__restrict__ rec, int64_t rec_origin,
   using Dt = Dot<KP, FULL>;
   constexpr int L = Dt::L, QL = Dt::QL;
   constexpr int RPS = 64 / L;
-  constexpr int UNR = rmse_unroll<KP>();
+  constexpr int UNR = rmse_unroll<KP>(FEW);
+  constexpr bool kFence = KP == 32 || (KP >= 64 && FEW);
   const int32_t p = G.p;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int grp = lane / L;
@@ -218,6 +253,7 @@ k_rmse_stratum(const uint2 *__restrict__ rec, int64_t rec_origin,
         dot.load(ua[u], row_ptr(Ub, min(r.x & kRowMask, rmax), rowbytes));
         dot.load(va[u], row_ptr(Vb, min((r.x >> kColShift) & kColMask, cmax), rowbytes));
       }
+      if constexpr (kFence) loads_issued();
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
         float d = dot.error(x[u], ua[u], va[u]);
@@ -494,8 +530,12 @@ hipError_t launch_rmse_kp(const uint2 *rec, const int64_t *wblock_ptr, const flo
     *count = (int64_t)p * kLdsWaves;
   } else {
     const int64_t groups = (int64_t)p * ((p + kRmseColGroup - 1) / kRmseColGroup);
-    hipLaunchKernelGGL((k_rmse_partial<KP, FULL>), dim3((unsigned)groups), dim3(256), 0, stream,
-                       rec, wblock_ptr, U, V, G, k, partials);
+    constexpr bool kByWaves = KP >= 64;  // narrower rows: one variant
+    auto f = kByWaves && groups * kWavesPerGroup <= few_waves<KP>()
+                 ? k_rmse_partial<KP, FULL, kByWaves>
+                 : k_rmse_partial<KP, FULL, false>;
+    hipLaunchKernelGGL(f, dim3((unsigned)groups), dim3(256), 0, stream, rec, wblock_ptr, U, V, G,
+                       k, partials);
     *count = groups * kWavesPerGroup;
   }
   return hipGetLastError();
@@ -535,8 +575,14 @@ hipError_t rmse_stratum_add(const uint2 *rec, int64_t rec_origin, const int64_t 
   const dim3 grid((unsigned)((p + kWavesPerGroup - 1) / kWavesPerGroup),
                   (unsigned)std::min(kRmseStrataGroups, s1 - s0));
   return with_width(k, [&](auto w, auto full) {
-    hipLaunchKernelGGL((k_rmse_stratum<decltype(w)::value, decltype(full)::value>), grid, dim3(256),
-                       0, stream, rec, rec_origin, block_ptr, s0, s1, U, V, G, k, partials);
+    constexpr int KP = decltype(w)::value;
+    constexpr bool FULL = decltype(full)::value;
+    const int64_t waves = (int64_t)grid.x * grid.y * kWavesPerGroup;
+    constexpr bool kByWaves = KP >= 64;
+    auto f = kByWaves && waves <= kStratumFewWaves ? k_rmse_stratum<KP, FULL, kByWaves>
+                                            : k_rmse_stratum<KP, FULL, false>;
+    hipLaunchKernelGGL(f, grid, dim3(256), 0, stream, rec, rec_origin, block_ptr, s0, s1, U, V, G,
+                       k, partials);
     return hipGetLastError();
   });
 }

@@ -47,3 +47,32 @@ def test_counts_and_widths(k, n):
             mdl.set_factors(U, V)
             mdl.load_coo(rows, cols, vals)
             assert abs(mdl.rmse() - ref) <= tol * ref
+
+
+@pytest.mark.parametrize("k", [16, 32, 48, 64, 128, 256])
+def test_many_blocks(k):
+    """A grid whose launches take one wave step at a time from k = 48 up
+    (p = 1056: 71,808 waves in-core, 16,896 streamed) with U rows too many
+    for LDS; the grids above take two."""
+    from paper_2304_13724_amd import bgmf
+    rng = np.random.default_rng(k)
+    p, nnz = 1056, 60_000
+    n, m = p * (41_000 // k + 1), p + 7
+    U = rng.random((n, k), dtype=np.float32)
+    V = rng.random((m, k), dtype=np.float32)
+    # half of the ratings in a few blocks, so that some are longer than a step
+    rows = np.r_[rng.integers(0, n, nnz // 2), rng.integers(0, 3 * n // p, nnz // 2)].astype(np.int32)
+    cols = np.r_[rng.integers(0, m, nnz // 2), rng.integers(0, 6, nnz // 2)].astype(np.int32)
+    vals = rng.integers(1, 6, nnz).astype(np.float32)
+    ref = _ref(rows, cols, vals, U, V)
+    # a dot is about k / 4 with at most k roundings of its size
+    tol = k * 2.0 ** -24 * (k / 4) / ref
+    got = []
+    for budget in (0, 2 << 20):
+        with bgmf.Model(n, m, k, p) as mdl:
+            mdl.set_option(bgmf.BGMF_OPT_RATINGS_BUDGET, budget)
+            mdl.set_factors(U, V)
+            mdl.load_coo(rows, cols, vals)
+            assert (mdl.get_option(bgmf.BGMF_OPT_STREAM_SLOTS) > 0) == bool(budget)
+            got.append(mdl.rmse())
+            assert abs(got[-1] - ref) <= tol * ref, (budget, got[-1], ref)

@@ -65,3 +65,34 @@ def test_heldout_grid_is_resident(kernels):
     assert len(coo) == 8
     for name in coo:
         assert kernels[name][0]["VGPRs"] <= 128, (name, kernels[name][0])
+
+
+def _loads_together(body):
+    """Most 16-byte row loads issued with no multiply-add between them."""
+    best = now = 0
+    for line in body:
+        if line.startswith("global_load_dwordx4"):
+            now += 1
+            best = max(best, now)
+        elif line.startswith(("v_fma_f32", "v_fmac_f32")):
+            now = 0
+    return best
+
+
+def test_row_loads_are_issued_together(kernels):
+    """A wave step's rows (u and v, one slice per lane at k = 16, else four)
+    are all requested before the first product, where the kernel fences them;
+    the compiler sinks them to their uses otherwise."""
+    checked = 0
+    for name, (_, body) in kernels.items():
+        if name[0] not in ("k_rmse_partial", "k_rmse_stratum"):
+            continue
+        kp, few = name[1], name[3]
+        partial = name[0] == "k_rmse_partial"
+        if not ((partial and kp <= 64) or kp == 32 or (kp >= 64 and few)):
+            continue
+        steps = 8 if kp == 16 else 2 if kp == 32 or few else 1
+        want = steps * 2 * (1 if kp == 16 else 4)
+        assert _loads_together(body) >= want, (name, _loads_together(body), want)
+        checked += 1
+    assert checked == 17
