@@ -57,6 +57,12 @@ constexpr int rmse_unroll(bool few) { return KP >= 64 ? (few ? 2 : 1) : KP >= 32
 template <int KP, bool FULL>
 constexpr int rmse_unroll_lds() { return KP < 32 ? 2 : FULL ? 3 : 1; }
 
+// Ratings of a block are counted in 32 bits without a sign: there are fewer
+// than 2^31, and a position at most kAhead past the last one (the loops' step
+// and the records fetched ahead) does not wrap.
+constexpr uint32_t kAhead = 4096;
+static_assert(0x7FFFFFFFu + kAhead > 0x7FFFFFFFu, "positions past the end compare as such");
+
 // Factor rows are addressed in bytes: a 64-bit base plus row * rowbytes is
 // one multiply-add.
 __device__ __forceinline__ const char *row_ptr(const float *base, uint32_t row, uint32_t rowbytes) {
@@ -161,24 +167,25 @@ k_rmse_partial(const uint2 *__restrict__ rec, const int64_t *__restrict__ wblock
     if (beg == end) continue;
     const float *Vb = V + G.col_start(c) * k;
     const uint32_t cmax = (uint32_t)(G.col_start(c + 1) - G.col_start(c)) - 1u;
-    const int32_t len = (int32_t)(end - beg);
+    const uint32_t len = (uint32_t)(end - beg);
+    static_assert((2 * UNR + 1) * RPS <= kAhead, "positions do not wrap");
     const uint2 *rb = rec + beg;
     // records of the next iteration are loaded one iteration ahead, so the
     // factor-row loads never wait for a record load
     uint2 rn[UNR];
 #pragma unroll
     for (int u = 0; u < UNR; ++u) {
-      const int32_t t = u * RPS + grp;
+      const uint32_t t = u * RPS + grp;
       rn[u] = rb[t < len ? t : 0];
     }
-    for (int32_t t0 = 0; t0 < len; t0 += RPS * UNR) {
+    for (uint32_t t0 = 0; t0 < len; t0 += RPS * UNR) {
       float4 ua[UNR][QL], va[UNR][QL];
       float x[UNR];
       uint2 r[UNR];
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
         r[u] = rn[u];
-        const int32_t t = t0 + (UNR + u) * RPS + grp;
+        const uint32_t t = t0 + (UNR + u) * RPS + grp;
         rn[u] = rb[t < len ? t : 0];
       }
 #pragma unroll
@@ -237,17 +244,18 @@ k_rmse_stratum(const uint2 *__restrict__ rec, int64_t rec_origin,
   double acc = 0.0;
   for (int32_t s = s0 + (int32_t)blockIdx.y; s < s1; s += (int32_t)gridDim.y) {
     const int64_t beg = block_ptr[(int64_t)s * p + b];
-    const int32_t len = (int32_t)(block_ptr[(int64_t)s * p + b + 1] - beg);
+    const uint32_t len = (uint32_t)(block_ptr[(int64_t)s * p + b + 1] - beg);
+    static_assert((UNR + 1) * RPS <= kAhead, "positions do not wrap");
     const uint2 *rb = rec + (beg - rec_origin);
     const int C = (b + s) % p;
     const float *Vb = V + G.col_start(C) * k;
     const uint32_t cmax = (uint32_t)(G.col_start(C + 1) - G.col_start(C)) - 1u;
-    for (int32_t t0 = 0; t0 < len; t0 += RPS * UNR) {
+    for (uint32_t t0 = 0; t0 < len; t0 += RPS * UNR) {
       float4 ua[UNR][QL], va[UNR][QL];
       float x[UNR];
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
-        const int32_t t = t0 + u * RPS + grp;
+        const uint32_t t = t0 + u * RPS + grp;
         const uint2 r = rb[t < len ? t : 0];
         x[u] = __uint_as_float(r.y);
         dot.load(ua[u], row_ptr(Ub, min(r.x & kRowMask, rmax), rowbytes));
@@ -372,7 +380,8 @@ k_rmse_lds(const uint2 *__restrict__ rec, const int64_t *__restrict__ wblock_ptr
   constexpr int UNR = rmse_unroll_lds<KP, FULL>();
   const int32_t p = G.p;
   extern __shared__ float4 us[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int grp = lane / L;
   const Dt dot(lane % L, k);
   const uint32_t rowbytes = (uint32_t)k * 4u;
@@ -400,11 +409,13 @@ k_rmse_lds(const uint2 *__restrict__ rec, const int64_t *__restrict__ wblock_ptr
     }
   }
   __syncthreads();
-  const int32_t T = bnd[p];
+  // The wave's ratings are [tb, tb + cnt) of the row-block's; t below is
+  // relative to tb (at most 2^31 / 16 ratings, so 32 bits hold every t).
+  const int32_t T = __builtin_amdgcn_readfirstlane(bnd[p]);
   const int32_t tb = (int32_t)((int64_t)T * wave / kLdsWaves);
-  const int32_t te = (int32_t)((int64_t)T * (wave + 1) / kLdsWaves);
+  const int32_t cnt = (int32_t)((int64_t)T * (wave + 1) / kLdsWaves) - tb;
   double acc = 0.0;
-  if (tb < te) {
+  if (cnt > 0) {
     // block of the wave's first rating: the last s with bnd[s] <= tb
     int32_t lo = 0, hi = p - 1;
     while (lo < hi) {
@@ -413,9 +424,9 @@ k_rmse_lds(const uint2 *__restrict__ rec, const int64_t *__restrict__ wblock_ptr
       else hi = mid - 1;
     }
     int32_t sg = lo;           // block of the lane group's current rating
-    int32_t nb = bnd[sg + 1];  // start of the block after it
+    int32_t nb = bnd[sg + 1] - tb;  // start of the block after it
     int2 ct = ctab[sg];
-    const uint2 *rb = rec + W0;
+    const uint2 *rb = rec + W0 + tb;
     // The records of an iteration are loaded two iterations ahead and turned
     // into row addresses one iteration ahead, while the rows of the current
     // one are on their way, so no load waits for another.
@@ -427,18 +438,18 @@ k_rmse_lds(const uint2 *__restrict__ rec, const int64_t *__restrict__ wblock_ptr
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
         const int32_t t = t0 + u * RPS + grp;
-        rn[u] = rb[t < te ? t : tb];
+        rn[u] = rb[t < cnt ? t : 0];
       }
     };
     auto decode = [&](int32_t t0) {
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
         const int32_t t = t0 + u * RPS + grp;
-        // step to the block of rating t (past empty blocks); te <= bnd[p]
-        if (t < te && t >= nb) {
+        // step to the block of rating t (past empty blocks); tb + cnt <= bnd[p]
+        if (t < cnt && t >= nb) {
           do {
             ++sg;
-            nb = bnd[sg + 1];
+            nb = bnd[sg + 1] - tb;
           } while (t >= nb);
           ct = ctab[sg];
         }
@@ -448,10 +459,10 @@ k_rmse_lds(const uint2 *__restrict__ rec, const int64_t *__restrict__ wblock_ptr
                         rowbytes);
       }
     };
-    fetch(tb);
-    decode(tb);
-    fetch(tb + RPS * UNR);
-    for (int32_t t0 = tb; t0 < te; t0 += RPS * UNR) {
+    fetch(0);
+    decode(0);
+    fetch(RPS * UNR);
+    for (int32_t t0 = 0; t0 < cnt; t0 += RPS * UNR) {
       float4 ua[UNR][QL], va[UNR][QL];
       float x[UNR];
 #pragma unroll
@@ -465,7 +476,7 @@ k_rmse_lds(const uint2 *__restrict__ rec, const int64_t *__restrict__ wblock_ptr
 #pragma unroll
       for (int u = 0; u < UNR; ++u) {
         float d = dot.error(x[u], ua[u], va[u]);
-        d = t0 + u * RPS + grp < te ? d : 0.0f;
+        d = t0 + u * RPS + grp < cnt ? d : 0.0f;
         acc = fma((double)d, (double)d, acc);
       }
     }

@@ -408,8 +408,10 @@ __global__ void __launch_bounds__(256) k_sgd_lds(SgdParams P) {
     //   wx   = x / KPL
     uint32_t wrow = 0u, wcol = spare;
     float wx = 0.0f;
-    auto decode = [&](uint2 w, int32_t c) {
-      const bool ok = c + lane < len;
+    // (positions past the end of a block of up to 2^31 - 1 ratings need the
+    // 32nd bit: unsigned here, and pointer sums where records are read)
+    auto decode = [&](uint2 w, uint32_t c) {
+      const bool ok = c + (uint32_t)lane < (uint32_t)len;
       wrow = ok ? (w.x & kRowMask) * rowbytes : 0u;
       wcol = ok ? ((w.x >> kColShift) & kColMask) * colbytes : spare;
       wx = __uint_as_float(w.y) * xscale;
@@ -519,7 +521,7 @@ __global__ void __launch_bounds__(256) k_sgd_lds(SgdParams P) {
         const int32_t left = TAIL ? tail_left(len, c) : CH;
         // records c .. c+63 are decoded and those of chunk c+CH are in
         // flight; fetch the window two chunks ahead now
-        const uint2 Wn2 = rp[c + 2 * CH + lane];
+        const uint2 Wn2 = (rp + c + 2 * CH)[lane];
 #pragma unroll
         for (int j = 0; j < CH; ++j) {
           const int slot = (j == 0) ? CH - 1 : j - 1;  // ring slot of the previous rating
@@ -605,7 +607,7 @@ __global__ void __launch_bounds__(256) k_sgd_lds(SgdParams P) {
             if (j + 1 >= left) break;
           }
         }
-        decode(Wn1, c + CH);
+        decode(Wn1, (uint32_t)c + CH);
         Wn1 = Wn2;
       };
 
@@ -632,7 +634,7 @@ __global__ void __launch_bounds__(256) k_sgd_lds(SgdParams P) {
       auto chunk_fold = [&](auto tail_tag, int32_t c) {
         constexpr bool TAIL = decltype(tail_tag)::value;
         const int32_t left = TAIL ? tail_left(len, c) : CH;
-        const uint2 Wn2 = rp[c + 2 * CH + lane];
+        const uint2 Wn2 = (rp + c + 2 * CH)[lane];
 #pragma unroll
         for (int j = 0; j < CH; ++j) {
           const int slot = (j == 0) ? CH - 1 : j - 1;  // ring slot of rating t - 1
@@ -713,7 +715,7 @@ __global__ void __launch_bounds__(256) k_sgd_lds(SgdParams P) {
             if (j + 1 >= left) break;
           }
         }
-        decode(Wn1, c + CH);
+        decode(Wn1, (uint32_t)c + CH);
         Wn1 = Wn2;
       };
 
@@ -871,11 +873,14 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
     int32_t t0 = 0;
     uint32_t wrow = 0u, wcol = 0u;
     float wx = 0.0f;
-    auto decode = [&](uint2 w, int32_t c) {
-      const int32_t t = c - CH + lane;
-      const bool ok = t >= t0 && t < len;
+    // (positions are relative to t0 and unsigned, as in k_sgd_lds; the CH
+    // before t0 wrap to the largest values)
+    auto decode = [&](uint2 w, uint32_t c) {
+      const uint32_t t = c - CH + (uint32_t)lane - (uint32_t)t0;
+      const bool ok = t < (uint32_t)(len - t0);
       wrow = ok ? (w.x & kRowMask) * rowbytes : 0u;
-      wcol = ok ? ((w.x >> kColShift) & kColMask) * rowbytes : (t < t0 ? kNoCol : 0u);
+      wcol = ok ? ((w.x >> kColShift) & kColMask) * rowbytes
+                : (t >= 0u - (uint32_t)CH ? kNoCol : 0u);
       wx = __uint_as_float(w.y) * xscale;
     };
 
@@ -889,7 +894,7 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
       decode(Wc, 0);
       Wn1 = rp[lane];  // window of chunk CH
     };
-    auto advance = [&](int32_t c, uint2 Wn2) {  // to the window of chunk c
+    auto advance = [&](uint32_t c, uint2 Wn2) {  // to the window of chunk c
       Wc = Wn1;
       decode(Wc, c);
       Wn1 = Wn2;
@@ -974,7 +979,7 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
           pnz[v] = z[v];  // the first pending store writes rating t's row back unchanged
         }
         auto step_chunk = [&](int32_t c) {
-          const uint2 Wn2 = rp[c + CH + lane];
+          const uint2 Wn2 = (rp + c + CH)[lane];
 #pragma unroll
           for (int j = 0; j < CH; ++j) {
             const int slot = (j == 0) ? CH - 1 : j - 1;  // ring slot of the previous rating
@@ -1033,7 +1038,7 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
             x64 = x64n;
             pin();
           }
-          advance(c + CH, Wn2);
+          advance((uint32_t)c + CH, Wn2);
           wz = by_row ? wcol : wrow;
           // the load of the next chunk's step 0
           const uint64_t hit =
@@ -1094,7 +1099,7 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
         constexpr bool TAIL = decltype(tail_tag)::value;
         const int32_t left = TAIL ? tail_left(len, c) : CH;
         // window of chunk c + 2 CH (ratings c + CH .. c + CH + 63)
-        const uint2 Wn2 = rp[c + CH + lane];
+        const uint2 Wn2 = (rp + c + CH)[lane];
         uint32_t ccur = rl(wcol, CH);
 #pragma unroll
         for (int j = 0; j < CH; ++j) {
@@ -1145,7 +1150,7 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
             if (j + 1 >= left) break;  // the block's last rating is done
           }
         }
-        advance(c + CH, Wn2);
+        advance((uint32_t)c + CH, Wn2);
       };
       // One float per lane (k <= 64): the same step with the stores of a
       // rating's results deferred into the next rating's reduction and every
@@ -1175,7 +1180,7 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
       auto chunk_pinned = [&](auto tail_tag, int32_t c) {
         constexpr bool TAIL = decltype(tail_tag)::value;
         const int32_t left = TAIL ? tail_left(len, c) : CH;
-        const uint2 Wn2 = rp[c + CH + lane];
+        const uint2 Wn2 = (rp + c + CH)[lane];
 #pragma unroll
         for (int j = 0; j < CH; ++j) {
           const int next = (j + 1) % D;  // ring slot of the next rating
@@ -1257,13 +1262,13 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
             if (j + 1 >= left) break;  // the block's last rating is done
           }
         }
-        advance(c + CH, Wn2);
+        advance((uint32_t)c + CH, Wn2);
       };
       // full chunks up to the block's end or the start of a run, then the
       // last, partial chunk
       int32_t c = seg;
       bool stop = false;
-      while (c + CH <= len) {
+      while (len - c >= CH) {
         if constexpr (NV == 1) chunk_pinned(std::false_type{}, c);
         else chunk(std::false_type{}, c);
         c += CH;
