@@ -934,21 +934,48 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
       // general step, which is bound by its issue slots); the arithmetic is
       // the general step's, so the results are the same bits.
       // A partner that repeats within the prefetch distance (a duplicate
-      // rating) ends the run before the chunk in which it would be stale.
+      // rating) ends the run before the chunk in which it would be stale; a
+      // run with one in its first two chunks would not pay for its entry and
+      // is not taken (blocks of 2,000 ratings of one row, k = 64: 8 columns
+      // in all 160 ns per rating when such a run was entered and left again,
+      // 117 now and 117 without a run to look at; 400 columns 110 and 102).
       //
       // run_at: does a run start at rating c (the window's lane CH)?
       auto run_at = [&](int32_t c) -> int {
         if (len - c < kRunMin) return 0;
         constexpr uint64_t kAll = ((1ull << kRunMin) - 1ull) << CH;
-        static_assert(kRunMin >= CH && CH + kRunMin <= 64, "the window shows a run's first ratings");
+        static_assert(kRunMin == 2 * CH && CH + kRunMin <= 64, "the window shows a run's first ratings");
+        int kind = kRunRow;
         const uint64_t rows = __builtin_amdgcn_ballot_w64(wrow == rl(wrow, CH));
-        if ((rows & kAll) == kAll) return kRunRow;
-        const uint64_t cols = __builtin_amdgcn_ballot_w64(wcol == rl(wcol, CH));
-        return (cols & kAll) == kAll ? kRunCol : 0;
+        if ((rows & kAll) != kAll) {
+          const uint64_t cols = __builtin_amdgcn_ballot_w64(wcol == rl(wcol, CH));
+          if ((cols & kAll) != kAll) return 0;
+          kind = kRunCol;
+        }
+        // Two equal partners in one of the run's first two chunks (a row of
+        // 16 lanes each): the rotations by 1 to 8 meet every pair of a row.
+        // (A pair across the two is met by the run, which then ends between
+        // them.)  Other lanes hold values of their own.
+        const uint32_t z = (kAll >> lane & 1) ? (kind == kRunRow ? wcol : wrow) : ~(uint32_t)lane;
+        uint32_t m = ~0u;
+        auto meet = [&](auto r) {
+          m = min(m, z ^ (uint32_t)__builtin_amdgcn_update_dpp(
+                             0, (int)z, 0x120 + decltype(r)::value, 0xF, 0xF, true));  // row_ror
+        };
+        meet(std::integral_constant<int, 1>{});
+        meet(std::integral_constant<int, 2>{});
+        meet(std::integral_constant<int, 3>{});
+        meet(std::integral_constant<int, 4>{});
+        meet(std::integral_constant<int, 5>{});
+        meet(std::integral_constant<int, 6>{});
+        meet(std::integral_constant<int, 7>{});
+        meet(std::integral_constant<int, 8>{});
+        const uint64_t hit = __builtin_amdgcn_ballot_w64(m == 0u);
+        if (hit == 0) return kind;
+        return 0;
       };
       // Sweeps the run that starts at t (whose window is decoded), in whole
-      // chunks; returns the first rating it leaves (whose window is decoded),
-      // or t if its first chunk has a duplicate.
+      // chunks; returns the first rating it leaves (whose window is decoded).
       auto run = [&](int32_t t, bool by_row) -> int32_t {
         const auto rows_of = [&](bool of_v) {  // the block's rows of V or U
           const int64_t base = reinterpret_cast<int64_t>(of_v ? P.V + c0 * k : P.U + r0 * k);
@@ -967,9 +994,7 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
         for (int j = 0; j < D; ++j) {
           ringrow[j] = rl(wz, CH + j);
           ld_row<NV, 0>(ring[j], Zres, doff, ringrow[j]);
-          dup |= (uint32_t)(__builtin_amdgcn_ballot_w64(wz == ringrow[j]) >> CH) & ((1u << j) - 1u);
         }
-        if (dup) return t;
         float x64 = __uint_as_float(rl(__float_as_uint(wx), CH));
         uint32_t poff = ringrow[0];
         __builtin_amdgcn_s_waitcnt(0x0F70);
@@ -1071,10 +1096,8 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
       while (seg < len) {
       if constexpr (!COH) {
         if (runs) {
-          const int kind = run_at(seg);
-          const int32_t next = kind ? run(seg, __builtin_amdgcn_readfirstlane(kind) == kRunRow) : seg;
-          if (next > seg) {
-            seg = next;
+          if (const int kind = run_at(seg)) {
+            seg = run(seg, __builtin_amdgcn_readfirstlane(kind) == kRunRow);
             continue;
           }
           if (seg > 0) {  // a new segment: the ratings before it match no column

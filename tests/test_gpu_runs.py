@@ -98,3 +98,33 @@ def test_heavy_users_and_items(schedule):
     w = _workload(rows[order], cols[order], 64, p, 9)
     _same_bits(w, schedule=schedule)
     _same_bits(w, schedule=schedule, budget=20_000)
+
+
+def test_duplicates_keep_the_general_pace():
+    """Blocks full of duplicate ratings have no run to sweep and take as long
+    as blocks of the same length without runs: looking for one costs 1%, one
+    entered and left again at every chunk cost 40%."""
+    from paper_2304_13724_amd import bgmf
+    p, width, length = 16, 2048, 2000
+    rng = np.random.default_rng(3)
+    blocks = [(R, C) for R in range(p) for C in range(0, p, 4)]
+    rows = {"duplicates": np.zeros(length, int), "single": np.arange(length) // 8}
+    cols = {"duplicates": lambda: rng.integers(0, 8, length),
+            "single": lambda: rng.permutation(width)[:length]}
+    ms = {}
+    for kind in rows:
+        r = np.concatenate([rows[kind] + R * width for R, _ in blocks])
+        c = np.concatenate([cols[kind]() + C * width for _, C in blocks])
+        w = _workload(np.r_[r, p * width - 1], np.r_[c, p * width - 1], 64, p, 7)
+        with bgmf.Model(w.n, w.m, w.k, w.p) as mdl:
+            mdl.set_option(bgmf.BGMF_OPT_V_STAGING, GLOBAL)
+            mdl.set_factors(w.U0, w.V0)
+            mdl.load_coo(w.rows, w.cols, w.vals)
+            times = []
+            for _ in range(8):
+                mdl.epoch(1e-4, 0.05)
+                mdl.sync()
+                times.append(mdl.timing()[0])
+        ms[kind] = min(times)
+    print(ms, flush=True)
+    assert ms["duplicates"] <= 1.15 * ms["single"]
