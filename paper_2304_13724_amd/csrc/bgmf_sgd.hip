@@ -817,14 +817,14 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
   constexpr int CH = D;
   static_assert(D == 16, "the window holds the previous chunk, the current one and the next two");
   constexpr int VPOL = COH ? kCoherent : 0;
-  // Shortest run swept as one, and shortest block in which runs are looked
-  // for.  Entering and leaving a run each wait for its first rows (about
-  // 1 us together, what 32 ratings gain): runs from 16 up take 107.2 ms per
-  // epoch of 100M ratings at k = 128, p = 2048, from 24 up 106.3 ms, from 32
-  // up 106.1 ms (and 115.6, 116.6, 116.3 ms at 20M ratings, k = 64, p = 4096;
-  // without runs 120.0 and 165.1 ms).
+  // Shortest run swept as one.  Entering and leaving a run each wait for its
+  // first rows, about 1 us together, what 32 ratings gain.  When the line was
+  // drawn, runs from 16 up took 107.2 ms per epoch of 100M ratings at k = 128,
+  // p = 2048, from 24 up 106.3 ms, from 32 up 106.1 ms (and 115.6, 116.6,
+  // 116.3 ms at 20M ratings, k = 64, p = 4096; without runs 120.0 and 165.1
+  // ms).  A least block length of 48, 64 or 96 ratings for looking at all
+  // changes neither by 0.1%.
   constexpr int kRunMin = 32;
-  constexpr int kRunBlock = 48;
   constexpr int kRunRow = 1, kRunCol = 2;
   constexpr uint32_t kNoCol = 0xFFFFFFFFu;  // column of ratings before the block: matches none
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -878,9 +878,19 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
     auto decode = [&](uint2 w, uint32_t c) {
       const uint32_t t = c - CH + (uint32_t)lane - (uint32_t)t0;
       const bool ok = t < (uint32_t)(len - t0);
-      wrow = ok ? (w.x & kRowMask) * rowbytes : 0u;
-      wcol = ok ? ((w.x >> kColShift) & kColMask) * rowbytes
-                : (t >= 0u - (uint32_t)CH ? kNoCol : 0u);
+      const uint32_t none = t >= 0u - (uint32_t)CH ? kNoCol : 0u;
+      // masks where runs are looked for: the compiler makes the choice a
+      // branch, which costs the general step 2% beside the look for a run;
+      // in the persistent form masks make it spill (blocks of 46 ratings,
+      // k = 128: 163 against 158 ns per rating)
+      if constexpr (COH) {
+        wrow = ok ? (w.x & kRowMask) * rowbytes : 0u;
+        wcol = ok ? (w.x >> kColShift) * rowbytes : none;
+      } else {
+        const uint32_t in = ok ? ~0u : 0u;
+        wrow = __umul24(w.x & kRowMask, rowbytes) & in;
+        wcol = (__umul24(w.x >> kColShift, rowbytes) & in) | none;
+      }
       wx = __uint_as_float(w.y) * xscale;
     };
 
@@ -906,11 +916,9 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
         ld_row<NV, 0>(ring[j], Ures, doff, ringrow[j]);
       }
     };
-    // blocks in which runs are looked for (see below)
-    const bool runs = !COH && len >= kRunBlock;
     if (len > 0) {
       open();
-      if (!runs) prime();
+      if constexpr (COH) prime();
     }
     if (s > P.s_begin) {
       const int nb = (b + 1 == P.p) ? 0 : b + 1;
@@ -940,14 +948,20 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
       // in all 160 ns per rating when such a run was entered and left again,
       // 117 now and 117 without a run to look at; 400 columns 110 and 102).
       //
-      // run_at: does a run start at rating c (the window's lane CH)?
-      auto run_at = [&](int32_t c) -> int {
-        if (len - c < kRunMin) return 0;
+      // Does a run start at rating c (the window's lane CH)?  Every chunk of
+      // the general step asks, so the first look (ends) only compares the
+      // first and the last of the run's ratings: rows ascend, so equal ends
+      // are one row.  Blocks without runs take 112.4 ns per rating at k = 64
+      // and 131.6 at k = 128 (with a full look at every chunk 114.5 and
+      // 145.1, without runs 108.5 and 128.5).
+      auto ends = [&]() { return rl(Wc.x, CH) ^ rl(Wc.x, CH + kRunMin - 1); };
+      auto may_run = [&](uint32_t x) { return min(x & kRowMask, x >> kColShift) == 0u; };
+      auto run_at = [&](int32_t c, uint32_t x) -> int {
+        if (len - c < kRunMin || !may_run(x)) return 0;
         constexpr uint64_t kAll = ((1ull << kRunMin) - 1ull) << CH;
         static_assert(kRunMin == 2 * CH && CH + kRunMin <= 64, "the window shows a run's first ratings");
         int kind = kRunRow;
-        const uint64_t rows = __builtin_amdgcn_ballot_w64(wrow == rl(wrow, CH));
-        if ((rows & kAll) != kAll) {
+        if (x & kRowMask) {
           const uint64_t cols = __builtin_amdgcn_ballot_w64(wcol == rl(wcol, CH));
           if ((cols & kAll) != kAll) return 0;
           kind = kRunCol;
@@ -1093,20 +1107,20 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
       for (int pass = 0; pass < P.passes; ++pass) {
       int32_t seg = 0;
       if (pass > 0) open();
+      int kind = COH ? 0 : run_at(0, ends());  // of the run that starts at seg
       while (seg < len) {
       if constexpr (!COH) {
-        if (runs) {
-          if (const int kind = run_at(seg)) {
-            seg = run(seg, __builtin_amdgcn_readfirstlane(kind) == kRunRow);
-            continue;
-          }
-          if (seg > 0) {  // a new segment: the ratings before it match no column
-            t0 = seg;
-            decode(Wc, seg);
-          }
+        if (kind) {
+          seg = run(seg, kind == kRunRow);
+          kind = run_at(seg, ends());
+          continue;
+        }
+        if (seg > 0) {  // a new segment: the ratings before it match no column
+          t0 = seg;
+          decode(Wc, seg);
         }
       }
-      if (runs || pass > 0) prime();
+      if (!COH || pass > 0) prime();
 #pragma unroll
       for (int j = 0; j < D; ++j) ld_row<NV, VPOL>(vring[j], Vres, doff, rl(wcol, CH + j));
       uint32_t prev_row = 0xFFFFFFFFu;
@@ -1285,24 +1299,27 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
             if (j + 1 >= left) break;  // the block's last rating is done
           }
         }
+        // (the last step's results stay in its place: the compiler would
+        // move them past the look for a run that follows, which needs none)
+        asm volatile("" : "+v"(u[0]), "+v"(vv[0]), "+v"(pnu[0]), "+v"(pnv[0]));
         advance((uint32_t)c + CH, Wn2);
       };
       // full chunks up to the block's end or the start of a run, then the
       // last, partial chunk
       int32_t c = seg;
-      bool stop = false;
       while (len - c >= CH) {
         if constexpr (NV == 1) chunk_pinned(std::false_type{}, c);
         else chunk(std::false_type{}, c);
         c += CH;
         if constexpr (!COH) {
-          if (runs && run_at(c)) {
-            stop = true;
-            break;
+          const uint32_t x = ends();
+          if (__builtin_expect(may_run(x), 0)) {
+            kind = run_at(c, x);
+            if (kind) break;
           }
         }
       }
-      if (!stop && c < len) {
+      if (!kind && c < len) {
         if constexpr (NV == 1) chunk_pinned(std::true_type{}, c);
         else chunk(std::true_type{}, c);
         c = len;

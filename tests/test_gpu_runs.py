@@ -1,8 +1,7 @@
 """Runs in the sweep with V in global memory: 32 or more consecutive ratings
-of one row or one column in a block of 48 or more take a step that keeps that
-row of U or V in registers.  Its arithmetic is the general step's, so the
-result is compared bit for bit with the LDS-staged sweep's general step: run
-lengths at the edges of the run rule, of its chunks of 16 and of the window
+of one row or one column in a block take a step that keeps that row of U or V
+in registers.  Its arithmetic is the general step's, so the result is compared
+bit for bit with the LDS-staged sweep's general step: run lengths at the edges of the run rule, of its chunks of 16 and of the window
 that finds runs, duplicate ratings at every distance inside a run (a row
 prefetched 16 ratings ahead would be stale), runs next to each other, to
 other ratings and to the block's ends.
@@ -100,31 +99,48 @@ def test_heavy_users_and_items(schedule):
     _same_bits(w, schedule=schedule, budget=20_000)
 
 
+def _epoch_ms(kind, k, schedule=0):
+    """Best of eight epochs over 16 x 16 blocks, every fourth column-block
+    filled with blocks of 2,000 ratings: of one row and 8 columns, or of runs
+    of 8 ratings."""
+    from paper_2304_13724_amd import bgmf
+    p, width, length = 16, 2048, 2000
+    rng = np.random.default_rng(3)
+    rows, cols = [], []
+    for R in range(p):
+        for C in range(0, p, 4):
+            dup = kind == "duplicates"
+            rows.append((np.zeros(length, int) if dup else np.arange(length) // 8) + R * width)
+            cols.append((rng.integers(0, 8, length) if dup else rng.permutation(width)[:length])
+                        + C * width)
+    last = p * width - 1
+    w = _workload(np.r_[np.concatenate(rows), last], np.r_[np.concatenate(cols), last], k, p, 7)
+    with bgmf.Model(w.n, w.m, w.k, w.p) as mdl:
+        mdl.set_option(bgmf.BGMF_OPT_V_STAGING, GLOBAL)
+        mdl.set_option(bgmf.BGMF_OPT_SCHEDULE, schedule)
+        mdl.set_factors(w.U0, w.V0)
+        mdl.load_coo(w.rows, w.cols, w.vals)
+        times = []
+        for _ in range(8):
+            mdl.epoch(1e-4, 0.05)
+            mdl.sync()
+            times.append(mdl.timing()[0])
+    return min(times)
+
+
 def test_duplicates_keep_the_general_pace():
     """Blocks full of duplicate ratings have no run to sweep and take as long
     as blocks of the same length without runs: looking for one costs 1%, one
     entered and left again at every chunk cost 40%."""
-    from paper_2304_13724_amd import bgmf
-    p, width, length = 16, 2048, 2000
-    rng = np.random.default_rng(3)
-    blocks = [(R, C) for R in range(p) for C in range(0, p, 4)]
-    rows = {"duplicates": np.zeros(length, int), "single": np.arange(length) // 8}
-    cols = {"duplicates": lambda: rng.integers(0, 8, length),
-            "single": lambda: rng.permutation(width)[:length]}
-    ms = {}
-    for kind in rows:
-        r = np.concatenate([rows[kind] + R * width for R, _ in blocks])
-        c = np.concatenate([cols[kind]() + C * width for _, C in blocks])
-        w = _workload(np.r_[r, p * width - 1], np.r_[c, p * width - 1], 64, p, 7)
-        with bgmf.Model(w.n, w.m, w.k, w.p) as mdl:
-            mdl.set_option(bgmf.BGMF_OPT_V_STAGING, GLOBAL)
-            mdl.set_factors(w.U0, w.V0)
-            mdl.load_coo(w.rows, w.cols, w.vals)
-            times = []
-            for _ in range(8):
-                mdl.epoch(1e-4, 0.05)
-                mdl.sync()
-                times.append(mdl.timing()[0])
-        ms[kind] = min(times)
-    print(ms, flush=True)
-    assert ms["duplicates"] <= 1.15 * ms["single"]
+    duplicates, single = _epoch_ms("duplicates", 64), _epoch_ms("single", 64)
+    print(duplicates, single, flush=True)
+    assert duplicates <= 1.15 * single
+
+
+def test_blocks_without_runs_keep_their_pace():
+    """Looking for runs costs blocks that have none little: against the
+    persistent schedule, whose step is the same without the look, 2% at k =
+    128 (a full look at every chunk cost 11%)."""
+    looking, plain = _epoch_ms("single", 128), _epoch_ms("single", 128, schedule=2)
+    print(looking, plain, flush=True)
+    assert looking <= 1.07 * plain
