@@ -1,7 +1,7 @@
 """Loading: the sort's key width (32 bits with the records prepared ahead, 64
-bits without), at the two sides of its limit, in-core and streamed; and the
-host check of the ratings, whose vector loop and threads must still name the
-first bad rating.
+bits without), at the two sides of its limit, in-core, and of a group of a
+streamed load; and the host check of the ratings, whose vector loop and threads
+must still name the first bad rating.
 """
 import numpy as np
 import pytest
@@ -20,7 +20,8 @@ def _cuts(n, p):
 @pytest.mark.parametrize("budget", [0, 100_000])
 def test_key_width(p, budget):
     """Row keys of 16 bits: with p = 255 the slots take 16 more (32 in all),
-    with p = 256 one more."""
+    with p = 256 one more.  (The streamed loads sort groups of about 1,100
+    slots, keys of 27 bits.)"""
     from paper_2304_13724_amd import bgmf
     rng = np.random.default_rng(p)
     rc, n = _cuts(0, p)
@@ -48,6 +49,45 @@ def test_key_width(p, budget):
     assert np.array_equal(bp, obp) and np.array_equal(perm, operm)
     # the records, through the RMSE that reads them: dots in binary32 (16
     # terms), squares in binary64
+    d = vals - (U[rows].astype(np.float64) * V[cols]).sum(1)
+    ref = float(np.sqrt((d * d).mean()))
+    assert abs(r - ref) <= 16 * 2.0 ** -24 * ref
+
+
+@pytest.mark.parametrize("span", [65_535, 65_536])
+def test_key_width_of_a_streamed_group(span):
+    """A group of a streamed load spans at most budget / 128 slots, and 65,536
+    of them (17 bits with the end marker) are one too many for 32 bits beside
+    rows of 16.  The crowded strata come first, so the group that reaches the
+    span starts after others; 12,000 ratings in the other 84,000 slots do not
+    limit it."""
+    from paper_2304_13724_amd import bgmf
+    p, k = 300, 16
+    rng = np.random.default_rng(300)
+    rc, n = _cuts(0, p)
+    m = 3 * p + 1
+    cc = np.array([(c * m + p - 1) // p for c in range(p + 1)], dtype=np.int64)
+    s = np.r_[rng.integers(0, 20, 252_000), rng.integers(20, p, 12_000)]
+    R = rng.integers(0, p, s.size)
+    C = (R + s) % p
+    order = rng.permutation(s.size)
+    rows = np.where(R == 0, rng.integers(0, 65_536, s.size), 65_535 + R)[order].astype(np.int32)
+    cols = (cc[C] + rng.integers(0, 3, s.size))[order].astype(np.int32)
+    vals = rng.integers(1, 6, s.size).astype(np.float32)
+    obp, operm = oracle.bucket_cuts(n, m, p, rc, cc, rows, cols)
+    U = rng.uniform(0, 0.1, (n, k)).astype(np.float32)
+    V = rng.uniform(0, 0.1, (m, k)).astype(np.float32)
+    with bgmf.Model(n, m, k, p) as mdl:
+        mdl.set_cuts(rc, cc)
+        mdl.set_option(bgmf.BGMF_OPT_RATINGS_BUDGET, 128 * span)
+        mdl.set_factors(U, V)
+        mdl.load_coo(rows, cols, vals)
+        assert mdl.get_option(bgmf.BGMF_OPT_STREAM_SLOTS) > 0
+        # four of crowded slots alone, the one that reaches the span, the rest
+        assert mdl.get_option(bgmf.BGMF_OPT_LOAD_GROUPS) == 6
+        bp, perm = mdl.get_layout()
+        r = mdl.rmse()
+    assert np.array_equal(bp, obp) and np.array_equal(perm, operm)
     d = vals - (U[rows].astype(np.float64) * V[cols]).sum(1)
     ref = float(np.sqrt((d * d).mean()))
     assert abs(r - ref) <= 16 * 2.0 ** -24 * ref

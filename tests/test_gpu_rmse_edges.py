@@ -42,10 +42,11 @@ def test_counts_and_widths(k, n):
             dev = [torch.from_numpy(a).cuda() for a in (rows, cols, vals)]
             torch.cuda.synchronize()
             assert bgmf.bgmf_rmse_coo_dev(mdl.h, *[t.data_ptr() for t in dev], nnz) == host
-        with bgmf.Model(n, m, k, p) as mdl:  # streamed
-            mdl.set_option(bgmf.BGMF_OPT_RATINGS_BUDGET, 1 << 17)
+        with bgmf.Model(n, m, k, p) as mdl:  # streamed: room for both strata, not for the load
+            mdl.set_option(bgmf.BGMF_OPT_RATINGS_BUDGET, 2 * 8 * (nnz + 256) + 64)
             mdl.set_factors(U, V)
             mdl.load_coo(rows, cols, vals)
+            assert mdl.get_option(bgmf.BGMF_OPT_STREAM_SLOTS) > 0
             assert abs(mdl.rmse() - ref) <= tol * ref
 
 

@@ -25,15 +25,16 @@ def _workload(rows, cols, k, p, seed):
     return Workload("runs", n, m, k, p, 0.01, 0.05, 1, rows, cols, vals, U0, V0)
 
 
-def _same_bits(w, **kw):
-    a = gpu_run(w, 2, v_staging=LDS, single=0)
-    g = gpu_run(w, 2, v_staging=GLOBAL, **kw)
+def _same_bits(w, passes=1, **kw):
+    a = gpu_run(w, 2, v_staging=LDS, single=0, passes=passes)
+    g = gpu_run(w, 2, v_staging=GLOBAL, passes=passes, **kw)
     assert np.array_equal(g[0], a[0]) and np.array_equal(g[1], a[1])
 
 
-def _block(by_row, length, before, after, dup):
+def _block(by_row, length, before, after, dup, at=None):
     """One block: `before` single ratings, a run of `length`, `after` single
-    ratings.  `dup`: the run's partner repeats `dup` ratings later, once."""
+    ratings.  `dup`: the run's partner repeats `dup` ratings later, once, in a
+    run of a row from rating `at` of the run (a third into it)."""
     rng = np.random.default_rng(1000 * length + dup)
     rows, cols = [], []
     for i in range(before):
@@ -43,7 +44,8 @@ def _block(by_row, length, before, after, dup):
         part = rng.permutation(90)[: min(length, 90)]
         part = np.r_[part, rng.permutation(200)[: length - part.size] + 90]
         if dup and dup < length:
-            at = length // 3 if length // 3 + dup < length else 0
+            if at is None:
+                at = length // 3 if length // 3 + dup < length else 0
             part[at + dup] = part[at]
         rows += [before] * length
         cols += [int(x) for x in part]
@@ -85,10 +87,33 @@ def test_duplicates_in_a_run(dup):
     _same_bits(_workload(rows, cols, 64, 1, dup))
 
 
-@pytest.mark.parametrize("schedule", [0, 1])
+@pytest.mark.parametrize("at", [0, 1, 14, 15, 16, 17, 30, 31])
+def test_duplicates_where_a_run_starts(at):
+    """Around the two chunks of 16 in which a duplicate refuses the run."""
+    for dup in (1, 8, 15, 16, 17):
+        rows, cols = _block(True, 70, 0, 3, dup, at)
+        _same_bits(_workload(rows, cols, 64, 1, at + dup))
+
+
+@pytest.mark.parametrize("passes", [2, 3])
+@pytest.mark.parametrize("k", [64, 128])
+def test_several_passes(passes, k):
+    """A pass starts again from rows the one before stored: after a run that
+    ends with the block, before one that starts it, and with a duplicate that
+    ends one."""
+    for by_row in (True, False):
+        for length, before, after, dup in ((64, 0, 0, 0), (64, 5, 0, 0), (70, 0, 9, 0),
+                                           (97, 16, 3, 7 if by_row else 1)):
+            rows, cols = _block(by_row, length, before, after, dup)
+            _same_bits(_workload(rows, cols, k, 1, length + passes), passes=passes)
+
+
+@pytest.mark.parametrize("schedule", [0, 2])
 def test_heavy_users_and_items(schedule):
     """Several blocks, each with a heavy user and a heavy item among other
-    ratings; two passes per block too, and the ratings streamed."""
+    ratings: one launch per stratum, which has runs, and the persistent
+    schedule, which has none; two passes per block too, and the ratings
+    streamed."""
     rng = np.random.default_rng(5)
     n, m, p = 600, 400, 4
     rows = np.r_[np.repeat([10, 310], m), np.tile(np.arange(n), 2), rng.integers(0, n, 1500)]
@@ -96,6 +121,7 @@ def test_heavy_users_and_items(schedule):
     order = rng.permutation(rows.size)
     w = _workload(rows[order], cols[order], 64, p, 9)
     _same_bits(w, schedule=schedule)
+    _same_bits(w, schedule=schedule, passes=2)
     _same_bits(w, schedule=schedule, budget=20_000)
 
 
