@@ -35,9 +35,10 @@ __device__ __forceinline__ int64_t gid() {
 
 // Key of a rating: (slot - q0, local row).  Every rating's slot lies in
 // [q0, q0 + nq); a slot outside it gets the key nq (past every table) and
-// raises the layout error.  K is 32 bits wide where the key fits (every
-// in-core grid up to p = 1024 with rows in proportion), which halves the
-// sort's key traffic; the scratch this frees holds the finished record of
+// raises the layout error.  K is 32 bits wide where the key fits,
+// bits(rows_max) + bits(nq + 1) <= 32 (in-core nq = p^2: 2,048 rows per block
+// at p = 1024, 512 at p = 2048; a streamed load's group has fewer slots),
+// which halves the sort's key traffic; the scratch this frees holds the finished record of
 // each rating (pay), so the gather after the sort reads one random 8-byte
 // word per rating instead of its column and value.
 template <class K>
@@ -286,7 +287,8 @@ __global__ void k_transpose(const int64_t *__restrict__ count, int32_t p,
 template <class K>
 __global__ void k_gather(const K *__restrict__ skeys, const int32_t *__restrict__ perm,
                          const int32_t *__restrict__ cols, const float *__restrict__ vals,
-                         const uint2 *__restrict__ pay, int64_t nnz, Grid G, int rbits, int64_t q0, int64_t nq,
+                         const uint2 *__restrict__ pay, int64_t nnz, Grid G, int rbits,
+                         int64_t q0, int64_t nq,
                          const int64_t *__restrict__ block_ptr,
                          const int64_t *__restrict__ wblock_ptr, bool stratum_major,
                          uint2 *__restrict__ rec, uint8_t *__restrict__ nofold, int32_t *err) {

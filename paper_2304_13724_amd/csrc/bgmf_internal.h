@@ -130,7 +130,7 @@ size_t rmse_partials_count(int32_t p);
 // vals of nnz ratings); partials must hold rmse_coo_partials_count() doubles.
 // *bad is cleared first (by a kernel), then receives bit 1 for a rating
 // outside the n x m matrix and bit 2 for a non-finite value (such ratings
-// are skipped without reading factors).
+// add nothing, and no row outside U or V is read).
 constexpr int kRmseCooGroups = 1024;
 size_t rmse_coo_partials_count();
 hipError_t launch_rmse_coo(const int32_t *rows, const int32_t *cols, const float *vals,

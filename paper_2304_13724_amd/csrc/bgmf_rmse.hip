@@ -278,8 +278,8 @@ k_rmse_stratum(const uint2 *__restrict__ rec, int64_t rec_origin,
 // same dot products and fp64 squares, with a lane group per rating taken
 // from a fixed grid-stride order, and one partial per wave.  A rating whose
 // row or column lies outside the matrix, or whose value is not finite, adds
-// nothing and sets a bit of *bad (1: index, 2: value); its factor rows are
-// not read.
+// nothing and sets a bit of *bad (1: index, 2: value); row 0 is read in the
+// place of a row that does not exist.
 //
 // The rows of U and V are random reads, so the kernel is bound by how many
 // of them are in flight: a wave has the rows of kCooUnroll steps outstanding
@@ -364,9 +364,13 @@ __global__ void k_zero(double *x, int64_t count) {
 // block starts and column-blocks in LDS gives the block of each rating (a
 // lane group steps its block forward as its ratings cross block starts), so
 // no block boundary waits for memory.  Used when the rows and the tables
-// fit in LDS.  Bound by the vector cache, which returns the v rows (256
-// bytes per rating at k = 64): 1.30 ms for 100M ratings, of which 0.92
-// remain without those loads, while the LDS reads cost nothing on top.
+// fit in LDS.  100M ratings, k = 64: 1.27 ms.  The vector cache's data return
+// is busy for 83% of all CU cycles, as long as the CUs are (the v rows alone,
+// 256 bytes per rating at 64 bytes per cycle, take 0.72 ms); its address unit
+// for 79%, LDS for 51% (36% bank conflicts: the rating groups of a wave read
+// the same 64-byte piece of their rows together), the vector ALUs for 38%.
+// Without the v loads 0.92 of 1.30 ms remained, so the units share the time:
+// with one workgroup on a CU their work overlaps only in part.
 constexpr int kLdsWaves = 16;
 
 template <int KP, bool FULL>

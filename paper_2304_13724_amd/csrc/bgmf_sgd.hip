@@ -937,10 +937,11 @@ __global__ void __launch_bounds__(256) k_sgd_gv(SgdParams P) {
       // partner rows of the other matrix (z), all different, come through
       // the ring.  The step needs no lookup of recent results, one load, one
       // store and three lane reads instead of six, and no choice between
-      // operands, so it runs at the pace of its dependency chain (66 ns per
-      // rating at k = 64 and 80 ns at k = 128, against 106 and 120 ns of the
-      // general step, which is bound by its issue slots); the arithmetic is
-      // the general step's, so the results are the same bits.
+      // operands, so it runs at the pace of its dependency chain (69 ns per
+      // rating at k = 64 and 79 ns at k = 128 in blocks of 2,000, against 112
+      // and 132 ns of the general step, which is bound by its issue slots);
+      // the arithmetic is the general step's, so the results are the same
+      // bits.
       // A partner that repeats within the prefetch distance (a duplicate
       // rating) ends the run before the chunk in which it would be stale; a
       // run with one in its first two chunks would not pay for its entry and
